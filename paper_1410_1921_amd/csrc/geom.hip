@@ -805,7 +805,8 @@ size_t diam_ws_bytes_n(const int32_t n[3]) {
     c.take<int32_t>(g.nvox());
     c.take<CellInfo>(cells);
     chords.take<uint32_t>((size_t)ChordWords(g).total());
-    return std::max(c.off, chords.off);
+    // never below the 12 bytes a voxel that this workspace has always asked for
+    return std::max({c.off, chords.off, 12 * (size_t)g.nvox()});
 }
 }  // namespace lbm
 
