@@ -62,17 +62,17 @@ struct alignas(16) FlowHalf {
     float a, b;
 };
 
+// Beside it, what a pull across the half's ends needs: the ids (-1 solid) of the voxels
+// before its first and after its last voxel, periodic in x, and the references there.
+struct alignas(16) FlowEdge {
+    float r_prev, r_next;
+    int32_t id_prev, id_next;
+};
+
 __host__ __device__ inline int64_t half_index(int64_t seg, int x) { return 2 * seg + ((x >> 5) & 1); }
 __device__ inline float half_ref(float a, float b, int x) {
     return __builtin_fmaf(b, (float)(x & 31), a);
 }
-// Node id at bit `bit` (= x % 64) of the half record holding it, or -1 for a solid voxel.
-__device__ inline int flow_lookup(const FlowHalf &h, int bit) {
-    const int b = bit & 31;
-    if (!((h.bits >> b) & 1u)) return -1;
-    return (int)(h.base + (uint32_t)__popc(h.bits & ((1u << b) - 1u)));
-}
-
 // Pressure boundaries: the populations entering through the inlet (e_x = +1) and the
 // outlet (e_x = -1), five each, and their slot in the ghost-plane buffer
 // [side][slot][ny nz].
@@ -139,11 +139,12 @@ struct FlowWs {
     uint32_t *coords;
     void *f[2];
     FlowHalf *fh;      // half-segment records with the references (binary32, binary16)
+    FlowEdge *fe;      // and their neighbours along x
     float2 *href_next; // references fitted at the last check, (a, b) per half segment
     float *dsnap;      // rho - 1 per node at the last check
     float *usnap;
     double *partials;
-    void *ghost;     // pressure boundaries: ghost-plane populations [2][5][ny nz]
+    void *ghost;     // pressure boundaries: two sets of ghost-plane populations [2][5][ny nz]
     int64_t stride;  // distance between population arrays (elements)
     size_t bytes;
 };
@@ -170,6 +171,7 @@ static FlowWs carve_flow(void *base, const Grid &g, int64_t nf, int32_t storage)
     w.rank = c.take<RankWord>(g.nsegs());
     const size_t nhalf = storage == LBM_STORE_FP64 ? 0 : 2 * (size_t)g.nsegs();
     w.fh = c.take<FlowHalf>(nhalf);
+    w.fe = c.take<FlowEdge>(2 * (size_t)g.nsegs());
     w.href_next = c.take<float2>(nhalf);
     w.samp_vox = c.take<int64_t>(kSampleMax);
     w.samp_out = c.take<double>((size_t)kSampleMax * 19);
@@ -182,7 +184,7 @@ static FlowWs carve_flow(void *base, const Grid &g, int64_t nf, int32_t storage)
     w.dsnap = c.take<float>(storage == LBM_STORE_FP64 ? 0 : (size_t)w.stride);
     w.usnap = c.take<float>((size_t)3 * w.stride);
     w.partials = c.take<double>((size_t)xcd_launch(blocks_for(nfp)) * kFlowSums);
-    w.ghost = c.take<double>((size_t)10 * g.ny * g.nz);
+    w.ghost = c.take<char>((size_t)2 * 10 * g.ny * g.nz * (storage == LBM_STORE_FP64 ? 8 : 4));
     w.bytes = c.off;
     return w;
 }
@@ -200,6 +202,7 @@ struct Sweep19 {
     const void *__restrict__ src;
     void *__restrict__ dst;
     const FlowHalf *__restrict__ fh;       // half records with the references read
+    const FlowEdge *__restrict__ fe;       // their neighbours along x
     const float2 *__restrict__ href_next;  // references written (when reframe)
     int reframe;                           // 1: write relative to href_next
     float *__restrict__ dsnap;             // check variant: rho - 1 per node
@@ -214,6 +217,8 @@ struct Sweep19 {
     int update_snap;
     int with_rho;                      // u_out carries a fourth plane, rho - 1
     const void *__restrict__ ghost;    // pressure boundaries: [2][5][ny nz] ghost populations
+    void *__restrict__ ghost_next;     // those of the state this sweep writes
+    double drho_in, drho_out;          // boundary densities less 1
 };
 
 // Kernel variants (chosen per solve from the working-set size, or forced):
@@ -392,34 +397,115 @@ __device__ inline void trt_collide(const R (&f)[19], R drho, R jx, R jy, R jz, R
     }
 }
 
-// The update of fluid node n at (x, y, z) whose 18 pull sources are resolved: ids[i] is
-// the node at x - e_i, -1 when that voxel is solid (half-way bounce-back), -2 a ghost
-// node beyond an x face (pressure boundaries); rs[i] the reference density at the source
-// (rs[0]: at the node), binary32 and binary16 storage.
+// The ghost node beyond boundary node b (pressure boundaries, Section 3.3; Guo's
+// non-equilibrium extrapolation): the five populations entering the domain, f(b) +
+// f_eq(rho_bc, u_b) - f_eq(rho_b, u_b), from b's state f (offsets from w_i (1 + ref)), into
+// ghost[side][slot][yz].  Without contraction, so that the sweep that writes b's state and
+// k_ghost19, which reads it, form the same bits.
+template <class T, class R>
+__device__ inline void ghost_node(const R (&f)[19], R ref, R Fx, R Fy, R Fz, R drho_in, R drho_out,
+                                  bool out, int64_t yz, int64_t m, T *__restrict__ ghost) {
+#pragma clang fp contract(off)
+    LBM_D3Q19_TABLES
+    LBM_GHOST_TABLES
+    R drho = 0, jx = 0, jy = 0, jz = 0;  // drho: offset from 1 + ref
+#pragma unroll
+    for (int i = 0; i < 19; i++) {
+        drho += f[i];
+        if (EX[i]) jx += EX[i] > 0 ? f[i] : -f[i];
+        if (EY[i]) jy += EY[i] > 0 ? f[i] : -f[i];
+        if (EZ[i]) jz += EZ[i] > 0 ? f[i] : -f[i];
+    }
+    // the density jump from the offsets (rho_bc - 1) - (rho_b - 1): both near 0, so
+    // binary32 keeps it to rounding (rho_bc - rho_b formed near 1 would lose ~1e-7)
+    const R rho = (R(1) + ref) + drho, jump = ((out ? drho_out : drho_in) - ref) - drho;
+    const R inv = R(1) / rho;
+    const R ux = (jx - R(0.5) * Fx) * inv, uy = (jy - R(0.5) * Fy) * inv, uz = (jz - R(0.5) * Fz) * inv;
+    const R base = R(1) - R(1.5) * (ux * ux + uy * uy + uz * uz);
+    const R un = out ? -ux : ux;
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        const int i = GIN[k];  // GOUT[k] is its mirror image in x
+        const R w = i < 7 ? R(1) / R(18) : R(1) / R(36);
+        R eu = un;
+        if (EY[i]) eu += EY[i] > 0 ? uy : -uy;
+        if (EZ[i]) eu += EZ[i] > 0 ? uz : -uz;
+        const R fi = out ? f[GOUT[k]] : f[GIN[k]];
+        const R v = fi + w * jump * (base + eu * (R(3) + R(4.5) * eu));
+        ghost[((out ? 5 : 0) + k) * m + yz] = (T)v;
+    }
+}
+
+// A 32-bit offset as a value of the current block, where its extension to 64 bits then is
+// part of the access (carried over from another block it costs a 64-bit addition each).
+__device__ inline uint32_t here(uint32_t o) {
+    asm("" : "+v"(o));
+    return o;
+}
+__device__ inline int64_t here(int64_t o) { return o; }
+
+// The node a population is pulled from: its id (meaningless unless fluid) and the
+// reference density there.
+struct Pull {
+    int id;
+    float r;
+    bool fluid;
+};
+
+// Byte offset of population 0 of node m, raised by 3 arrays of 256 so that the offset of
+// a neighbouring array (a bounced population is read from the opposite direction's) is
+// never negative; the array's own offset goes into the uniform base pointer.
+template <class T, class Off>
+__device__ inline Off pop_offset(int m) {
+    if constexpr (std::is_same<Off, uint32_t>::value)
+        return __umul24((uint32_t)m >> 8, 18u * 256u * (uint32_t)sizeof(T)) +
+               ((uint32_t)m * (uint32_t)sizeof(T) + 768u * (uint32_t)sizeof(T));
+    else
+        return (Off)((uint32_t)m >> 8) * (18 * 256 * (int64_t)sizeof(T)) +
+               ((int64_t)m * (int64_t)sizeof(T) + 768 * (int64_t)sizeof(T));
+}
+
+// An array's base address in scalar registers of its own, so that an access adds only its
+// 32-bit offset (the compiler would fold the array's constant into a 64-bit vector
+// addition per access).  Global address space: the base keeps it through the barrier.
+typedef __attribute__((address_space(1))) char gchar;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <class T>
+using gptr = __attribute__((address_space(1))) T *;
+__device__ inline gchar *array_base(const void *p) {
+    gchar *q = (gchar *)p;
+    asm("" : "+s"(q));
+    return q;
+}
+
+// The update of fluid node n at (x, y, z) whose 18 pull sources are resolved: src[i] is
+// the node at x - e_i, not fluid when that voxel is solid (half-way bounce-back); `ghost`
+// (pressure boundaries) has bit i set when it is a ghost node beyond an x face, src[i].r
+// then the reference of its boundary node.  r0: the reference at the node itself.
 template <class P, bool CHECK, bool NT, int COLL, bool OPEN, class Off>
 __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
-                              const int (&ids)[19], const float (&rs)[19],
-                              int64_t half_own, double (&acc)[kFlowSums]) {
+                              const Pull (&src)[19], uint32_t ghost, float r0, int64_t half_own,
+                              double (&acc)[kFlowSums]) {
     using T = typename P::T;
     using R = typename P::R;
     LBM_D3Q19_TABLES
     const R W0 = R(1) / R(3), W1 = R(1) / R(18), W2 = R(1) / R(36);
-    const T *__restrict__ src = static_cast<const T *>(a.src);
-    T *__restrict__ dst = static_cast<T *>(a.dst);
     const R omega = par<R>(a.omega, a.omega_d), fpre = par<R>(a.fpre, a.fpre_d);
     const R Fx = par<R>(a.Fx, a.Fd[0]), Fy = par<R>(a.Fy, a.Fd[1]), Fz = par<R>(a.Fz, a.Fd[2]);
-    // element offsets pop19(i, node): 32-bit while 19 * stride fits (fewer registers),
-    // 64-bit beyond
-    Off off[19];
-    off[0] = (Off)pop19(0, n);
-#pragma unroll
-    for (int i = 1; i < 19; i++)
-        off[i] = ids[i] >= 0 ? (Off)pop19(i, ids[i]) : (Off)pop19(OPP[i], n);
+    constexpr int64_t kArr = 256 * (int64_t)sizeof(T);  // bytes of an array of a block
+    const char *__restrict__ sb = static_cast<const char *>(a.src) - 3 * kArr;
+    char *__restrict__ db = static_cast<char *>(a.dst) - 3 * kArr;
+    const Off own = pop_offset<T, Off>((int)n);
     R f[19];
+    f[0] = from_store<P>(*(gptr<const T>)(array_base(sb) + own), a.inv_scale);
 #pragma unroll
-    for (int i = 0; i < 19; i++) f[i] = from_store<P>(src[off[i]], a.inv_scale);
+    for (int i = 1; i < 19; i++) {
+        const Off pulled = pop_offset<T, Off>(src[i].id), bounced = own + (Off)((OPP[i] - i) * kArr);
+        const Off o = src[i].fluid ? pulled : bounced;
+        f[i] = from_store<P>(*(gptr<const T>)(array_base(sb + i * kArr) + o), a.inv_scale);
+    }
     if constexpr (OPEN) {
-        // sources beyond an x face: the ghost planes of the pressure boundaries (-2), at
+        // sources beyond an x face: the ghost planes of the pressure boundaries, at
         // [side][slot][z_s ny + y_s] with (y_s, z_s) the source's row (periodic in y, z);
         // only the boundary nodes take this branch, so the indices are formed here
         LBM_GHOST_TABLES
@@ -428,7 +514,7 @@ __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
             const int ny = a.g.ny, nz = a.g.nz;
 #pragma unroll
             for (int i = 1; i < 19; i++) {
-                if (EX[i] == 0 || ids[i] != -2) continue;
+                if (EX[i] == 0 || !((ghost >> i) & 1u)) continue;
                 const int side = EX[i] == 1 ? 0 : 1;
                 int ys = y - EY[i], zs = z - EZ[i];
                 ys = ys < 0 ? ys + ny : (ys >= ny ? ys - ny : ys);
@@ -439,16 +525,17 @@ __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
     }
     constexpr bool kRef = !std::is_same<T, double>::value;
     if constexpr (kRef) {
-        // move pulled values to offsets from the node's own segment reference (sources in
-        // another segment; a ghost value is relative to its boundary node's segment,
-        // which rs[i] holds); the rest population and bounced ones are the node's own
+        // move pulled values to offsets from the node's own reference (a ghost value is
+        // relative to its boundary node's); the rest population and bounced ones are the
+        // node's own
 #pragma unroll
-        for (int i = 1; i < 19; i++)
-            if (ids[i] >= 0 || (OPEN && ids[i] == -2))  // one rounding, in every variant
-                f[i] = __builtin_fmaf(i < 7 ? 1.f / 18.f : 1.f / 36.f, rs[i] - rs[0], f[i]);
+        for (int i = 1; i < 19; i++) {
+            const bool moved = src[i].fluid || (OPEN && ((ghost >> i) & 1u));
+            const float dr = moved ? src[i].r - r0 : 0.f;
+            f[i] = __builtin_fmaf(i < 7 ? 1.f / 18.f : 1.f / 36.f, dr, f[i]);
+        }
     }
-
-    // drho: the density offset from 1 + rs[0] (from 1 for binary64)
+    // drho: the density offset from 1 + r0 (from 1 for binary64)
     R drho = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
     for (int i = 0; i < 19; i++) {
@@ -457,7 +544,7 @@ __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
         if (EY[i]) jy += EY[i] > 0 ? f[i] : -f[i];
         if (EZ[i]) jz += EZ[i] > 0 ? f[i] : -f[i];
     }
-    const R rho = kRef ? (R(1) + R(rs[0])) + drho : R(1) + drho;
+    const R rho = kRef ? (R(1) + R(r0)) + drho : R(1) + drho;
     const R inv = R(1) / rho;
     const R mx = jx + R(0.5) * Fx, my = jy + R(0.5) * Fy, mz = jz + R(0.5) * Fz;
     const R ux = mx * inv, uy = my * inv, uz = mz * inv;
@@ -485,21 +572,43 @@ __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
     if constexpr (kRef)
         if (a.reframe) {
             const float2 nx = a.href_next[half_own];
-            shift = R(rs[0]) - R(half_ref(nx.x, nx.y, x));
+            shift = R(r0) - R(half_ref(nx.x, nx.y, x));
         }
+    const Off at = here(own);
 #pragma unroll
     for (int i = 0; i < 19; i++) {
         const R w = i == 0 ? W0 : (i < 7 ? W1 : W2);
         R post = posts[i];
         if constexpr (kRef) post = __builtin_fmaf(w, shift, post);
+        if constexpr (OPEN) posts[i] = post;
         const T out = to_store<P>(post, a.scale);
+        gptr<T> dst = (gptr<T>)(array_base(db + i * kArr) + at);
         if (NT)
-            __builtin_nontemporal_store(out, &dst[pop19(i, n)]);
+            __builtin_nontemporal_store(out, dst);
         else
-            dst[pop19(i, n)] = out;
+            *dst = out;
+    }
+    if constexpr (OPEN) {
+        // the ghosts of this new state beside the boundary nodes (a kernel of its own before
+        // every sweep took 6.4 of a step's 25 us at 150 x 101 x 86)
+        if (x == 0 || x == a.g.nx - 1) {
+            R ref = R(0);
+            if constexpr (kRef) {
+                ref = R(r0);
+                if (a.reframe) {
+                    const float2 nx = a.href_next[half_own];
+                    ref = R(half_ref(nx.x, nx.y, x));
+                }
+            }
+            const int64_t m = (int64_t)a.g.ny * a.g.nz, yz = (int64_t)z * a.g.ny + y;
+            T *__restrict__ gh = static_cast<T *>(a.ghost_next);
+            ghost_node<T, R>(posts, ref, Fx, Fy, Fz, R(a.drho_in), R(a.drho_out), x != 0, yz, m, gh);
+            if (a.g.nx == 1)  // between both planes
+                ghost_node<T, R>(posts, ref, Fx, Fy, Fz, R(a.drho_in), R(a.drho_out), true, yz, m, gh);
+        }
     }
     if (CHECK) {
-        const R drho_abs = kRef ? R(rs[0]) + drho : drho;  // rho - 1
+        const R drho_abs = kRef ? R(r0) + drho : drho;  // rho - 1
         if constexpr (kRef) a.dsnap[n] = (float)drho_abs;
         const double dux = (double)ux - (double)a.usnap[n];
         const double duy = (double)uy - (double)a.usnap[a.stride + n];
@@ -509,7 +618,7 @@ __device__ inline void node19(const Sweep19 &a, int64_t n, int x, int y, int z,
         acc[2] += (double)jx + 0.5 * (double)Fx;
         acc[3] += (double)jy + 0.5 * (double)Fy;
         acc[4] += (double)jz + 0.5 * (double)Fz;
-        acc[5] += kRef ? (double)rs[0] + (double)drho : (double)drho;
+        acc[5] += kRef ? (double)r0 + (double)drho : (double)drho;
         if (a.update_snap) {
             a.usnap[n] = (float)ux;
             a.usnap[a.stride + n] = (float)uy;
@@ -536,79 +645,117 @@ __device__ inline void write_partials(double (&acc)[NV], int64_t row, bool valid
 }
 
 // The update of fluid node n (n < a.nf): its coordinates, the 18 pull sources from the
-// rank map (one batch of loads), then node19.
+// records of the nine rows around it, then node19.
+//
+// A row's fluid nodes are consecutive in the list, in x order.  So one record per row
+// (the half segment at the node's own x) gives all three sources of a row: with rank R =
+// base + popcount(bits below x), the node at x is R, at x - 1 R - 1 and at x + 1 R or
+// R + 1, each fluid if its bit says so; the reference is the same line.  Only the nodes at
+// the ends of a half (2 of 32) also load the half's edge record, one masked load per row
+// in the same batch.  With one record looked up per source (18 loads of 16 bytes, 64-bit
+// addresses, 927 vector instructions a wave against 726 now) the sweep took 5.9 us at 32^3,
+// 26.0 at 128^3 and 1105 at 512^3; now 5.0, 24.1 and 1050.
 template <class P, bool CHECK, bool NT, int COLL, bool OPEN, class Off>
 __device__ inline void sweep19_node(const Sweep19 &a, int64_t n, double (&acc)[kFlowSums]) {
     LBM_D3Q19_TABLES
-    LBM_GHOST_TABLES
+    constexpr bool kRef = !std::is_same<P, StoreF64>::value;
     const uint32_t c = a.coords[n];
     const int x = c & 1023, y = (c >> 10) & 1023, z = c >> 20;
     const Grid &g = a.g;
-    // per-axis pieces of the rank word and bit of x-1, x, x+1 (periodic, or with pressure
-    // boundaries the node's own x standing in beyond a face), etc.
-    int xs[3], ys[3], zs[3];
-    if (OPEN) {
-        xs[0] = x == 0 ? x : x - 1; xs[1] = x; xs[2] = x == g.nx - 1 ? x : x + 1;
-    } else {
-        xs[0] = x == 0 ? g.nx - 1 : x - 1; xs[1] = x; xs[2] = x == g.nx - 1 ? 0 : x + 1;
-    }
-    ys[0] = y == 0 ? g.ny - 1 : y - 1; ys[1] = y; ys[2] = y == g.ny - 1 ? 0 : y + 1;
-    zs[0] = z == 0 ? g.nz - 1 : z - 1; zs[1] = z; zs[2] = z == g.nz - 1 ? 0 : z + 1;
-    int wx[3], wy[3], wz[3], bx[3];
+    // byte offsets of the half records: rows of 2 nseg halves (at most 2^25 halves)
+    constexpr uint32_t kRec = kRef ? sizeof(FlowHalf) : sizeof(RankHalf);
+    const uint32_t nh = 2u * (uint32_t)g.nseg, sy = nh, sz = nh * (uint32_t)g.ny;
+    const uint32_t hx = (uint32_t)x >> 5;
+    uint32_t wy[3], wz[3];
+    wy[1] = __umul24((uint32_t)y, sy);
+    wy[0] = y == 0 ? wy[1] + (uint32_t)(g.ny - 1) * sy : wy[1] - sy;
+    wy[2] = y == g.ny - 1 ? 0u : wy[1] + sy;
+    wz[1] = __umul24((uint32_t)z, sz) + hx;
+    wz[0] = z == 0 ? wz[1] + (uint32_t)(g.nz - 1) * sz : wz[1] - sz;
+    wz[2] = z == g.nz - 1 ? hx : wz[1] + sz;
+    const int bit = x & 31;
+    const bool first = bit == 0, last = bit == 31 || x == g.nx - 1;
+    const char *recs = kRef ? reinterpret_cast<const char *>(a.fh) : reinterpret_cast<const char *>(a.rank);
+    uint32_t bits[9], base[9];
+    float ra[9], rb[9];
+    u32x4 ed[9];  // FlowEdge, of the lanes at the ends of a half only
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        wx[k] = xs[k] >> kSegLog;
-        wy[k] = ys[k] * g.nseg;
-        wz[k] = zs[k] * (g.ny * g.nseg);
-        bx[k] = xs[k] & (kSeg - 1);
+    for (int r = 0; r < 9; r++) {  // row (y + r % 3 - 1, z + r / 3 - 1)
+        const uint32_t h = wy[r % 3] + wz[r / 3];
+        if constexpr (kRef) {
+            const FlowHalf rec = *reinterpret_cast<const FlowHalf *>(recs + h * kRec);
+            bits[r] = rec.bits;
+            base[r] = rec.base;
+            ra[r] = rec.a;
+            rb[r] = rec.b;
+        } else {
+            const RankHalf rec = *reinterpret_cast<const RankHalf *>(recs + h * kRec);
+            bits[r] = rec.bits;
+            base[r] = rec.base;
+            ra[r] = rb[r] = 0.f;
+        }
     }
-    // the 18 rank records (with the references) are loaded as one batch, then the 19
-    // populations as another
-    constexpr bool kRef = !std::is_same<P, StoreF64>::value;
-    float rs[19];
-    int ids[19];
-    const int64_t half_own = half_index((int64_t)wx[1] + wy[1] + wz[1], x);
-    if constexpr (kRef) {
-        FlowHalf rh[19];
+    if (first || last) {
+        const gchar *edges = array_base(a.fe);
 #pragma unroll
-        for (int i = 1; i < 19; i++)
-            rh[i] = a.fh[half_index((int64_t)wx[1 - EX[i]] + wy[1 - EY[i]] + wz[1 - EZ[i]],
-                                    bx[1 - EX[i]])];
-        const float2 own = *reinterpret_cast<const float2 *>(&a.fh[half_own].a);
-        rs[0] = half_ref(own.x, own.y, x);
+        for (int r = 0; r < 9; r++)
+            if (r % 2 == 1 || r == 4)  // rows with sources at x - 1 and x + 1
+                ed[r] = *(gptr<const u32x4>)(edges + here((wy[r % 3] + wz[r / 3]) * (uint32_t)sizeof(FlowEdge)));
+    }
+    const uint32_t b0 = 1u << bit, below = b0 - 1u, bm = b0 >> 1, bp = last ? 0u : b0 << 1;
+    const float xf = (float)bit, xm = xf - 1.f, xp = xf + 1.f;
+    // beyond an x face with pressure boundaries
+    const bool gm = OPEN && x == 0, gp = OPEN && x == g.nx - 1;
+    Pull src[19];
+    src[0] = Pull{0, 0.f, true};
+    uint32_t ghost = 0;
+    float r0 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 9; r++) {
+        const int ey = 1 - r % 3, ez = 1 - r / 3;  // of the velocities pulled from this row
+        const int rank = (int)(base[r] + (uint32_t)__popc(bits[r] & below));
+        const bool f0 = (bits[r] & b0) != 0;
+        const float rc = __builtin_fmaf(rb[r], xf, ra[r]);
+        if (r == 4) r0 = rc;
 #pragma unroll
         for (int i = 1; i < 19; i++) {
-            ids[i] = flow_lookup(rh[i], bx[1 - EX[i]]);
-            rs[i] = half_ref(rh[i].a, rh[i].b, bx[1 - EX[i]]);
+            if (EY[i] != ey || EZ[i] != ez) continue;
+            if (EX[i] == 0) {
+                src[i] = Pull{rank, rc, f0};
+            } else if (EX[i] == 1) {  // from x - 1
+                const float rl = __builtin_fmaf(rb[r], xm, ra[r]);
+                const int il = (bits[r] & bm) ? rank - 1 : -1;
+                src[i].id = first ? (int)ed[r].z : il;
+                src[i].r = first ? __uint_as_float(ed[r].x) : rl;
+                src[i].fluid = src[i].id >= 0;
+                if (OPEN && gm) {  // a ghost beside a solid node is solid
+                    if (f0) ghost |= 1u << i;
+                    src[i].fluid = false;
+                    src[i].r = rc;
+                }
+            } else {  // from x + 1
+                const float rl = __builtin_fmaf(rb[r], xp, ra[r]);
+                const int il = (bits[r] & bp) ? rank + (f0 ? 1 : 0) : -1;
+                src[i].id = last ? (int)ed[r].w : il;
+                src[i].r = last ? __uint_as_float(ed[r].y) : rl;
+                src[i].fluid = src[i].id >= 0;
+                if (OPEN && gp) {
+                    if (f0) ghost |= 1u << i;
+                    src[i].fluid = false;
+                    src[i].r = rc;
+                }
+            }
         }
-    } else {
-        RankHalf rh[19];
-#pragma unroll
-        for (int i = 1; i < 19; i++)
-            rh[i] = rank_half(a.rank, (int64_t)wx[1 - EX[i]] + wy[1 - EY[i]] + wz[1 - EZ[i]],
-                              bx[1 - EX[i]]);
-#pragma unroll
-        for (int i = 0; i < 19; i++) rs[i] = 0.f;
-#pragma unroll
-        for (int i = 1; i < 19; i++) ids[i] = half_lookup(rh[i], bx[1 - EX[i]]);
     }
-    ids[0] = 0;
-#pragma unroll
-    for (int i = 1; i < 19; i++) {
-        if (OPEN && ((EX[i] == 1 && x == 0) || (EX[i] == -1 && x == g.nx - 1))) {
-            // the source is a ghost node; its boundary node (looked up at this x) decides:
-            // fluid -> the ghost's population, solid -> bounce back
-            ids[i] = ids[i] >= 0 ? -2 : -1;
-        }
-    }
-    node19<P, CHECK, NT, COLL, OPEN, Off>(a, n, x, y, z, ids, rs, half_own, acc);
+    node19<P, CHECK, NT, COLL, OPEN, Off>(a, n, x, y, z, src, ghost, kRef ? r0 : 0.f,
+                                          (int64_t)(wy[1] + wz[1]), acc);
 }
 
 // One stream-collide step, one fluid node per thread.  CHECK also forms the FP64 partial
 // sums of the convergence check and writes the velocity snapshot / field.
 template <class P, bool CHECK, bool NT, int COLL, bool OPEN, class Off>
 __global__ __launch_bounds__(256) void k_sweep19(Sweep19 a) {
-    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, a.chunk) : (int64_t)blockIdx.x;
+    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     const int64_t n = lb * 256 + threadIdx.x;
     double acc[kFlowSums] = {0, 0, 0, 0, 0, 0};
     if (n < a.nf) sweep19_node<P, CHECK, NT, COLL, OPEN, Off>(a, n, acc);
@@ -638,9 +785,9 @@ struct LatDesc {
     int64_t b0, b1;
 };
 
-template <bool CHECK, bool NT, int COLL>
+template <bool CHECK, bool NT, int COLL, class Off>
 __global__ __launch_bounds__(256) void k_sweep19b(Sweep19 a, const BlkDesc19 *__restrict__ descs) {
-    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, a.chunk) : (int64_t)blockIdx.x;
+    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     double acc[kFlowSums] = {0, 0, 0, 0, 0, 0};
     const bool live = lb < a.launched_live;
     int64_t pb = 0;
@@ -657,35 +804,29 @@ __global__ __launch_bounds__(256) void k_sweep19b(Sweep19 a, const BlkDesc19 *__
         b.src = static_cast<const float *>(a.src) + 19 * n0;
         b.dst = static_cast<float *>(a.dst) + 19 * n0;
         b.fh = a.fh + 2 * D.rk0;
+        b.fe = a.fe + 2 * D.rk0;
         b.href_next = a.href_next + 2 * D.rk0;
         b.dsnap = a.dsnap + n0;
         b.usnap = a.usnap + 3 * n0;
         b.u_out = D.u_out;
         const int64_t n = (pb - D.b0) * 256 + threadIdx.x;
-        if (n < D.nf) sweep19_node<StoreF32, CHECK, NT, COLL, false, uint32_t>(b, n, acc);
+        if (n < D.nf) sweep19_node<StoreF32, CHECK, NT, COLL, false, Off>(b, n, acc);
     }
     if (CHECK) write_partials<kFlowSums>(acc, pb, live, a.partials);
 }
 
-// Pressure boundaries (Section 3.3), Guo's non-equilibrium extrapolation: the ghost node
-// beyond boundary node b (x = 0 or nx - 1, same y, z) holds f(b) + f_eq(rho_bc, u_b) -
-// f_eq(rho_b, u_b), with rho_b, u_b the moments of b's state (u_b = (j - F/2)/rho_b, the
-// velocity of b's collision) and f_eq of Eq. 3; only the five populations entering the
-// domain are kept, as offsets from w_i (1 + r) with r the reference density at b (from
-// its half record fh; null for binary64 storage), in ghost[side][slot][z ny + y].  A
-// ghost beside a solid b is solid (the sweep bounces back) and is not written.
+// The ghost populations of a stored state (the sweeps form those of the states they
+// write): src relative to the references of fh (null for binary64 storage).  A ghost
+// beside a solid node is solid (the sweep bounces back) and is not written.
 template <class P>
 __global__ __launch_bounds__(256) void k_ghost19(Grid g, const RankWord *__restrict__ rank,
                                                  const typename P::T *__restrict__ src,
                                                  const FlowHalf *__restrict__ fh,
-                                                 float inv_scale, float scale,
                                                  typename P::R Fx, typename P::R Fy,
                                                  typename P::R Fz, typename P::R drho_in,
                                                  typename P::R drho_out,
                                                  typename P::T *__restrict__ ghost) {
     using R = typename P::R;
-    LBM_D3Q19_TABLES
-    LBM_GHOST_TABLES
     const int64_t m = (int64_t)g.ny * g.nz;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= 2 * m) return;
@@ -700,28 +841,10 @@ __global__ __launch_bounds__(256) void k_ghost19(Grid g, const RankWord *__restr
         const FlowHalf h = fh[half_index(g.seg(xb, y, z), xb)];
         ref = R(half_ref(h.a, h.b, xb));
     }
-    R f[19], drho = 0, jx = 0, jy = 0, jz = 0;  // drho: offset from 1 + ref
+    R f[19];
 #pragma unroll
-    for (int i = 0; i < 19; i++) {
-        f[i] = from_store<P>(src[pop19(i, id)], inv_scale);
-        drho += f[i];
-        jx += EX[i] * f[i];
-        jy += EY[i] * f[i];
-        jz += EZ[i] * f[i];
-    }
-    // the density jump from the offsets (rho_bc - 1) - (rho_b - 1): both near 0, so
-    // binary32 keeps it to rounding (rho_bc - rho_b formed near 1 would lose ~1e-7)
-    const R rho = (R(1) + ref) + drho, jump = ((side ? drho_out : drho_in) - ref) - drho;
-    const R ux = (jx - R(0.5) * Fx) / rho, uy = (jy - R(0.5) * Fy) / rho, uz = (jz - R(0.5) * Fz) / rho;
-    const R uu15 = R(1.5) * (ux * ux + uy * uy + uz * uz);
-#pragma unroll
-    for (int k = 0; k < 5; k++) {
-        const int i = side ? GOUT[k] : GIN[k];
-        const R w = i < 7 ? R(1) / R(18) : R(1) / R(36);
-        const R eu = EX[i] * ux + EY[i] * uy + EZ[i] * uz;
-        const R v = f[i] + w * jump * (R(1) + R(3) * eu + R(4.5) * eu * eu - uu15);
-        ghost[(side * 5 + k) * m + yz] = to_store<P>(v, scale);
-    }
+    for (int i = 0; i < 19; i++) f[i] = from_store<P>(src[pop19(i, id)], 1.f);
+    ghost_node<typename P::T, R>(f, ref, Fx, Fy, Fz, drho_in, drho_out, side != 0, yz, m, ghost);
 }
 
 // rho - 1 of the initial state per node: the fourth plane of u_init with with_rho, else 0
@@ -740,20 +863,32 @@ __global__ __launch_bounds__(256) void k_flow_drho0(Grid g, int64_t nf,
     dsnap[n] = dr;
 }
 
-// The half records from the rank map: occupancy and first node id of each half segment
-// (their references are written by k_ref_commit).
-__global__ __launch_bounds__(256) void k_flow_halves(int64_t nhalves,
-                                                     const RankWord *__restrict__ rank,
-                                                     FlowHalf *__restrict__ fh) {
+// The voxels before the first (k = 0) and after the last (k = 1) voxel of half h of a
+// lattice, periodic in x: their half and their x.
+__device__ inline int64_t edge_half(const Grid &g, int64_t h, int k, int &x) {
+    const int nh = 2 * g.nseg, hx = (int)(h % nh);
+    const int64_t row = h - hx;
+    if (k == 0) x = hx == 0 ? g.nx - 1 : 32 * hx - 1;
+    else x = 32 * hx + 32 >= g.nx ? 0 : 32 * hx + 32;
+    return row + (x >> 5);
+}
+
+// The half records from the rank map: occupancy and first node id of each half segment,
+// and the ids beyond its ends (their references are written by k_ref_commit; fh null for
+// binary64 storage, which has none).
+__global__ __launch_bounds__(256) void k_flow_halves(Grid g, const RankWord *__restrict__ rank,
+                                                     FlowHalf *__restrict__ fh,
+                                                     FlowEdge *__restrict__ fe) {
     const int64_t h = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (h >= nhalves) return;
-    const RankWord w = rank[h >> 1];
-    FlowHalf r;
-    r.bits = (h & 1) ? w.hi : w.lo;
-    r.base = (h & 1) ? w.base_hi : w.base;
-    r.a = 0.f;
-    r.b = 0.f;
-    fh[h] = r;
+    if (h >= 2 * g.nsegs()) return;
+    const RankHalf *__restrict__ rh = reinterpret_cast<const RankHalf *>(rank);
+    if (fh) {
+        const RankHalf w = rh[h];
+        fh[h] = FlowHalf{w.bits, w.base, 0.f, 0.f};
+    }
+    int x0, x1;
+    const RankHalf p = rh[edge_half(g, h, 0, x0)], q = rh[edge_half(g, h, 1, x1)];
+    fe[h] = FlowEdge{0.f, 0.f, half_lookup(p, x0), half_lookup(q, x1)};
 }
 
 // The reference of each half segment: the least-squares line a + b (x mod 32) through
@@ -786,13 +921,18 @@ __global__ __launch_bounds__(256) void k_half_fit(int64_t nhalves, const RankWor
 }
 
 // The references of the last check become those of the stored state.
-__global__ __launch_bounds__(256) void k_ref_commit(int64_t nhalves, const float2 *__restrict__ next,
-                                                    FlowHalf *__restrict__ fh) {
+__global__ __launch_bounds__(256) void k_ref_commit(Grid g, const float2 *__restrict__ next,
+                                                    FlowHalf *__restrict__ fh,
+                                                    FlowEdge *__restrict__ fe) {
     const int64_t h = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (h >= nhalves) return;
+    if (h >= 2 * g.nsegs()) return;
     const float2 r = next[h];
     fh[h].a = r.x;
     fh[h].b = r.y;
+    int x0, x1;
+    const float2 p = next[edge_half(g, h, 0, x0)], q = next[edge_half(g, h, 1, x1)];
+    fe[h].r_prev = half_ref(p.x, p.y, x0);
+    fe[h].r_next = half_ref(q.x, q.y, x1);
 }
 
 // The equilibrium (Eq. 3) of rho = 1 + drho and u from u_init (planes u_x, u_y, u_z and,
@@ -870,9 +1010,15 @@ struct Variant19 {
     bool wide;  // 64-bit population offsets
 };
 
+// 32-bit byte offsets reach all 19 arrays (pop_offset's highest, below 22 arrays of 256
+// past the last block's start).
+static bool narrow19(int64_t stride, int32_t storage) {
+    return (19 * stride + 768) * pop_bytes(storage) <= (int64_t)UINT32_MAX;
+}
+
 static Variant19 pick_variant(int32_t v, int64_t stride, int32_t storage) {
     Variant19 m;
-    m.wide = (v & LBM_VARIANT_OFF64) || 19 * stride > (int64_t)UINT32_MAX;
+    m.wide = (v & LBM_VARIANT_OFF64) || !narrow19(stride, storage);
     if (v & LBM_VARIANT_EXPLICIT) {
         m.remap = v & LBM_VARIANT_REMAP;
         m.nt = v & LBM_VARIANT_NTSTORE;
@@ -900,7 +1046,7 @@ static void launch19o(const Sweep19 &a, const Variant19 &m, hipStream_t s) {
 
 template <class P, bool CHECK, int COLL>
 static void launch19p(const Sweep19 &a, const Variant19 &m, hipStream_t s) {
-    if (m.wide || 19 * a.stride > (int64_t)UINT32_MAX) launch19o<P, CHECK, COLL, int64_t>(a, m, s);
+    if (m.wide) launch19o<P, CHECK, COLL, int64_t>(a, m, s);
     else launch19o<P, CHECK, COLL, uint32_t>(a, m, s);
 }
 
@@ -930,8 +1076,8 @@ static lbm_status launch_sweeps(const FlowWs &w, const Grid &g, int64_t nf, Flow
     a.g = g;
     a.nf = nf;
     a.stride = w.stride;
-    a.chunk = m.remap ? (blocks_for(nf) + kXcd - 1) / kXcd : 0;
-    a.launched = a.chunk ? xcd_launch(blocks_for(nf), a.chunk) : blocks_for(nf);
+    a.chunk = m.remap ? xcd_chunk(blocks_for(nf)) : 0;
+    a.launched = a.chunk ? xcd_launch(blocks_for(nf)) : blocks_for(nf);
     a.coords = w.coords;
     a.rank = w.rank;
     a.omega = (float)(1.0 / h.tau);
@@ -954,30 +1100,37 @@ static lbm_status launch_sweeps(const FlowWs &w, const Grid &g, int64_t nf, Flow
     a.dsnap = w.dsnap;
     const bool open = h.boundary == LBM_BOUNDARY_PRESSURE;
     a.ghost = open ? w.ghost : nullptr;
+    a.ghost_next = nullptr;
+    a.drho_in = h.rho_in - 1.0;
+    a.drho_out = h.rho_out - 1.0;
+    const int64_t gbytes = 10 * (int64_t)g.ny * g.nz * pop_bytes(h.storage);
     const unsigned gblocks = (unsigned)((2 * (int64_t)g.ny * g.nz + 255) / 256);
     for (int64_t t = 0; t < steps; t++) {
         a.src = w.f[cur];
         a.dst = w.f[cur ^ 1];
         a.reframe = 0;
         a.fh = h.sref ? w.fh : nullptr;
+        a.fe = w.fe;
         a.href_next = w.href_next;
         const bool reframe = h.sref && h.sref_pending;
         if (reframe) {
             a.reframe = 1;
             h.sref_pending = 0;
         }
-        if (open) {  // the ghost planes of this step, from the state it reads
+        if (open) {
+            a.ghost = static_cast<char *>(w.ghost) + (t & 1) * gbytes;
+            a.ghost_next = static_cast<char *>(w.ghost) + (~t & 1) * gbytes;
+        }
+        if (open && t == 0) {  // the ghost planes of the first step, from the state it reads
+            void *gh = static_cast<char *>(w.ghost);
             if (h.storage == LBM_STORE_FP64)
                 k_ghost19<StoreF64><<<gblocks, 256, 0, s>>>(
-                    g, w.rank, static_cast<const double *>(a.src), nullptr, 1.f, 1.f,
-                    h.force[0], h.force[1], h.force[2], h.rho_in - 1.0, h.rho_out - 1.0,
-                    static_cast<double *>(w.ghost));
+                    g, w.rank, static_cast<const double *>(a.src), nullptr, h.force[0], h.force[1],
+                    h.force[2], a.drho_in, a.drho_out, static_cast<double *>(gh));
             else
                 k_ghost19<StoreF32><<<gblocks, 256, 0, s>>>(
-                    g, w.rank, static_cast<const float *>(a.src), a.fh, 1.f, 1.f,
-                    (float)h.force[0], (float)h.force[1], (float)h.force[2],
-                    (float)(h.rho_in - 1.0), (float)(h.rho_out - 1.0),
-                    static_cast<float *>(w.ghost));
+                    g, w.rank, static_cast<const float *>(a.src), a.fh, a.Fx, a.Fy, a.Fz,
+                    (float)a.drho_in, (float)a.drho_out, static_cast<float *>(gh));
             LBM_CHECK_LAUNCH();
         }
         if (check_last && t == steps - 1)
@@ -988,7 +1141,7 @@ static lbm_status launch_sweeps(const FlowWs &w, const Grid &g, int64_t nf, Flow
         cur ^= 1;
         if (reframe) {  // the stored state is now relative to the new references
             const int64_t nh = 2 * g.nsegs();
-            k_ref_commit<<<(unsigned)((nh + 255) / 256), 256, 0, s>>>(nh, w.href_next, w.fh);
+            k_ref_commit<<<(unsigned)((nh + 255) / 256), 256, 0, s>>>(g, w.href_next, w.fh, w.fe);
             LBM_CHECK_LAUNCH();
         }
     }
@@ -1127,17 +1280,17 @@ extern "C" lbm_status lbm_flow_solve(const int32_t n[3], const uint8_t *fluid,
         const unsigned nb = (unsigned)blocks_for(nf);
         const float sc = (float)h.scale;
         const int wr = p->with_rho;
+        // the half records, with the first references fitted to the initial density
+        const unsigned nhb = (unsigned)((2 * g.nsegs() + 255) / 256);
+        k_flow_halves<<<nhb, 256, 0, s>>>(g, w.rank, h.sref ? w.fh : nullptr, w.fe);
+        LBM_CHECK_LAUNCH();
         if (h.sref) {
-            // the half records, with the first references fitted to the initial density
             const int64_t nh = 2 * g.nsegs();
-            const unsigned nhb = (unsigned)((nh + 255) / 256);
-            k_flow_halves<<<nhb, 256, 0, s>>>(nh, w.rank, w.fh);
-            LBM_CHECK_LAUNCH();
             k_flow_drho0<<<nb, 256, 0, s>>>(g, nf, w.coords, u_init, wr, w.dsnap);
             LBM_CHECK_LAUNCH();
             k_half_fit<<<nhb, 256, 0, s>>>(nh, w.rank, w.dsnap, w.href_next);
             LBM_CHECK_LAUNCH();
-            k_ref_commit<<<nhb, 256, 0, s>>>(nh, w.href_next, w.fh);
+            k_ref_commit<<<nhb, 256, 0, s>>>(g, w.href_next, w.fh, w.fe);
             LBM_CHECK_LAUNCH();
         }
         if (h.storage == LBM_STORE_FP16)
@@ -1342,6 +1495,7 @@ struct BatchWs {
     uint32_t *coords;
     float *f[2];
     FlowHalf *fh;       // half records with the references (rank-map order, 2 per segment)
+    FlowEdge *fe;       // and their neighbours along x
     float2 *href_next;
     float *dsnap;
     float *usnap;
@@ -1368,6 +1522,7 @@ static BatchWs carve_batch(void *base, int count, const int32_t *n_h, const int6
     w.res = c.take<double>((size_t)count * kFlowSums);
     w.rank = c.take<RankWord>(w.nrank);
     w.fh = c.take<FlowHalf>(2 * (size_t)w.nrank);
+    w.fe = c.take<FlowEdge>(2 * (size_t)w.nrank);
     w.href_next = c.take<float2>(2 * (size_t)w.nrank);
     w.coords = c.take<uint32_t>(w.stride);
     w.f[0] = c.take<float>((size_t)19 * w.stride);
@@ -1379,24 +1534,29 @@ static BatchWs carve_batch(void *base, int count, const int32_t *n_h, const int6
     return w;
 }
 
+template <bool CHECK, int COLL>
+static void launch19bc(const Sweep19 &a, const Variant19 &m, const BlkDesc19 *descs, hipStream_t s) {
+    const unsigned grid = (unsigned)a.launched;
+    if (m.wide) {  // some lattice is beyond 32-bit byte offsets
+        if (m.nt) k_sweep19b<CHECK, true, COLL, int64_t><<<grid, 256, 0, s>>>(a, descs);
+        else k_sweep19b<CHECK, false, COLL, int64_t><<<grid, 256, 0, s>>>(a, descs);
+    } else {
+        if (m.nt) k_sweep19b<CHECK, true, COLL, uint32_t><<<grid, 256, 0, s>>>(a, descs);
+        else k_sweep19b<CHECK, false, COLL, uint32_t><<<grid, 256, 0, s>>>(a, descs);
+    }
+}
+
 template <bool CHECK>
 static void launch19b(const Sweep19 &a, const Variant19 &m, int32_t collision,
                       const BlkDesc19 *descs, hipStream_t s) {
-    const unsigned grid = (unsigned)a.launched;
-    if (collision == LBM_COLLIDE_MRT) {
-        if (m.nt) k_sweep19b<CHECK, true, LBM_COLLIDE_MRT><<<grid, 256, 0, s>>>(a, descs);
-        else k_sweep19b<CHECK, false, LBM_COLLIDE_MRT><<<grid, 256, 0, s>>>(a, descs);
-    } else if (collision == LBM_COLLIDE_TRT) {
-        if (m.nt) k_sweep19b<CHECK, true, LBM_COLLIDE_TRT><<<grid, 256, 0, s>>>(a, descs);
-        else k_sweep19b<CHECK, false, LBM_COLLIDE_TRT><<<grid, 256, 0, s>>>(a, descs);
-    } else {
-        if (m.nt) k_sweep19b<CHECK, true, LBM_COLLIDE_BGK><<<grid, 256, 0, s>>>(a, descs);
-        else k_sweep19b<CHECK, false, LBM_COLLIDE_BGK><<<grid, 256, 0, s>>>(a, descs);
-    }
+    if (collision == LBM_COLLIDE_MRT) launch19bc<CHECK, LBM_COLLIDE_MRT>(a, m, descs, s);
+    else if (collision == LBM_COLLIDE_TRT) launch19bc<CHECK, LBM_COLLIDE_TRT>(a, m, descs, s);
+    else launch19bc<CHECK, LBM_COLLIDE_BGK>(a, m, descs, s);
 }
 
 // A lattice's place in the batch, for the per-lattice passes on the host side.
 struct LatRef {
+    Grid g;
     int64_t nsegs, rk0, n0;
 };
 
@@ -1410,13 +1570,14 @@ static lbm_status batch_steps(const BatchWs &w, Sweep19 a, const Variant19 &m, i
                               const std::vector<int32_t> &lat_ids_h, hipStream_t s) {
     const int64_t n_live = g.n_blk;
     a.launched_live = n_live;
-    a.chunk = m.remap ? (n_live + kXcd - 1) / kXcd : 0;
-    a.launched = a.chunk ? xcd_launch(n_live, a.chunk) : n_live;
+    a.chunk = m.remap ? xcd_chunk(n_live) : 0;
+    a.launched = a.chunk ? xcd_launch(n_live) : n_live;
     const BlkDesc19 *descs = w.descs + g.blk_off;
     for (int64_t t = 0; t < steps; t++) {
         a.src = w.f[cur];
         a.dst = w.f[cur ^ 1];
         a.fh = w.fh;
+        a.fe = w.fe;
         a.href_next = w.href_next;
         a.reframe = pending && t == 0;
         if (check_last && t == steps - 1) launch19b<true>(a, m, collision, descs, s);
@@ -1428,7 +1589,7 @@ static lbm_status batch_steps(const BatchWs &w, Sweep19 a, const Variant19 &m, i
                 const LatRef &L = lr[lat_ids_h[g.lat_off + k]];
                 const int64_t nh = 2 * L.nsegs;
                 k_ref_commit<<<(unsigned)((nh + 255) / 256), 256, 0, s>>>(
-                    nh, w.href_next + 2 * L.rk0, w.fh + 2 * L.rk0);
+                    L.g, w.href_next + 2 * L.rk0, w.fh + 2 * L.rk0, w.fe + 2 * L.rk0);
                 LBM_CHECK_LAUNCH();
             }
     }
@@ -1527,13 +1688,13 @@ extern "C" lbm_status lbm_flow_solve_batch(int32_t count, const int32_t *n_h,
         const int64_t b1 = b0 + blocks_for(nf), span = (b1 - b0) * 256;
         // from rest: the half records with every reference 0
         k_flow_halves<<<(unsigned)((2 * g.nsegs() + 255) / 256), 256, 0, s>>>(
-            2 * g.nsegs(), w.rank + rk0, w.fh + 2 * rk0);
+            g, w.rank + rk0, w.fh + 2 * rk0, w.fe + 2 * rk0);
         LBM_CHECK_LAUNCH();
         k_flow_init<StoreF32><<<(unsigned)blocks_for(nf), 256, 0, s>>>(
             g, nf, span, w.coords + n0, nullptr, 0, w.f[0] + 19 * n0, 1.f, w.fh + 2 * rk0,
             w.usnap + 3 * n0);
         LBM_CHECK_LAUNCH();
-        lref[l] = LatRef{g.nsegs(), rk0, n0};
+        lref[l] = LatRef{g, g.nsegs(), rk0, n0};
         float *uo = u_out ? u_out[l] : nullptr;
         if (uo) LBM_TRY_HIP(hipMemsetAsync(uo, 0, sizeof(float) * 3 * g.nvox(), s));
         lats[l] = LatDesc{b0, b1};
@@ -1565,8 +1726,13 @@ extern "C" lbm_status lbm_flow_solve_batch(int32_t count, const int32_t *n_h,
         return LBM_OK;
     };
     const int32_t vbits = p->variant & kVariantBits;
+    bool wide = false;  // offsets are those of a lattice's own run
+    for (int l = 0; l < count; l++)
+        wide = wide || !narrow19(blocks_for(nf_h[l]) * 256, LBM_STORE_FP32);
     auto group_mode = [&](const BatchGroup &g) {
-        return pick_variant(vbits, (int64_t)g.nodes, LBM_STORE_FP32);
+        Variant19 m = pick_variant(vbits, (int64_t)g.nodes, LBM_STORE_FP32);
+        m.wide = wide;
+        return m;
     };
     double live_nodes = 0.0;
     for (int l : act) live_nodes += (double)nf_h[l];

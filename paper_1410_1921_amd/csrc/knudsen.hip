@@ -250,7 +250,7 @@ __device__ inline void sweep7_node(const Sweep7 &a, int64_t n, double (&acc)[kKn
 // One step, one fluid node per thread.
 template <bool CHECK, bool NT, class Off>
 __global__ __launch_bounds__(256) void k_sweep7(Sweep7 a) {
-    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, a.chunk) : (int64_t)blockIdx.x;
+    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     const int64_t n = lb * 256 + threadIdx.x;
     double acc[kKnSums] = {0, 0, 0, 0, 0};
     if (n < a.nf) sweep7_node<CHECK, NT, Off>(a, n, acc);
@@ -359,7 +359,7 @@ __device__ inline void sweep19d_node(const Sweep7 &a, int64_t n, double (&acc)[k
 
 template <bool CHECK, bool NT, class Off>
 __global__ __launch_bounds__(256) void k_sweep19d(Sweep7 a) {
-    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, a.chunk) : (int64_t)blockIdx.x;
+    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     const int64_t n = lb * 256 + threadIdx.x;
     double acc[kKnSums] = {0, 0, 0, 0, 0};
     if (n < a.nf) sweep19d_node<CHECK, NT, Off>(a, n, acc);
@@ -397,7 +397,7 @@ static_assert(sizeof(KnBlk) == 64, "one record per launched block");
 
 template <bool CHECK, bool NT>
 __global__ __launch_bounds__(256) void k_sweep7b(Sweep7 a, const KnBlk *__restrict__ descs) {
-    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, a.chunk) : (int64_t)blockIdx.x;
+    const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     double acc[kKnSums] = {0, 0, 0, 0, 0};
     const bool live = lb < a.launched_live;
     int64_t pb = 0;
@@ -760,8 +760,8 @@ static lbm_status kn_launch(const KnWs &w, const Grid &g, int64_t nf, KnHeader &
     a.g = g;
     a.nf = nf;
     a.stride = w.stride;
-    a.chunk = m.remap ? (kn_blocks(nf) + kXcd - 1) / kXcd : 0;
-    a.launched = a.chunk ? xcd_launch(kn_blocks(nf), a.chunk) : kn_blocks(nf);
+    a.chunk = m.remap ? xcd_chunk(kn_blocks(nf)) : 0;
+    a.launched = a.chunk ? xcd_launch(kn_blocks(nf)) : kn_blocks(nf);
     a.coords = w.coords;
     a.rank = w.rank;
     a.omega = w.omega;
@@ -1202,8 +1202,8 @@ static lbm_status kn_batch_steps(const KnBatchWs &w, Sweep7 a, const Variant7 &m
                                  const lbm_knudsen_params *p, hipStream_t s) {
     const int64_t n_live = g.n_blk;
     a.launched_live = n_live;
-    a.chunk = m.remap ? (n_live + kXcd - 1) / kXcd : 0;
-    a.launched = a.chunk ? xcd_launch(n_live, a.chunk) : n_live;
+    a.chunk = m.remap ? xcd_chunk(n_live) : 0;
+    a.launched = a.chunk ? xcd_launch(n_live) : n_live;
     const KnBlk *descs = w.descs + g.blk_off;
     for (int64_t t = 0; t < steps; t++) {
         if (q.pending) {

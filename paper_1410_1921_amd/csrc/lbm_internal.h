@@ -101,20 +101,15 @@ constexpr int32_t kSolveVariantBits = kVariantBits | LBM_VARIANT_OFF64;
 
 // ---------------------------------------------------------------- XCD-aware mapping
 // Workgroups are dealt to the 8 XCDs round robin (workgroup b runs on XCD b % 8).
-// Remap so that each XCD walks runs of `chunk` consecutive logical blocks, the 8 XCDs
-// side by side: neighbouring rows of a column then share an L2.  The launch holds
-// xcd_launch(blocks, chunk) workgroups (a multiple of 8 * chunk, so the map is a
-// permutation of it); logical blocks >= blocks have no work.  chunk = ceil(blocks / 8)
-// gives each XCD one contiguous eighth of the list.
+// Remap so that each XCD walks one contiguous eighth of the list, `chunk` = ceil(blocks / 8)
+// consecutive blocks: neighbouring rows of a column then share an L2.  The launch holds
+// xcd_launch(blocks) = 8 chunk workgroups; logical blocks >= blocks have no work.
 constexpr int kXcd = 8;
-__device__ inline int64_t xcd_block(int64_t b, int64_t chunk) {
-    const int64_t x = b % kXcd, j = b / kXcd;
-    return (j / chunk) * (kXcd * chunk) + x * chunk + j % chunk;
+__device__ inline int64_t xcd_block(uint32_t b, uint32_t chunk) {
+    return (int64_t)((b % kXcd) * chunk + b / kXcd);
 }
-inline int64_t xcd_launch(int64_t blocks, int64_t chunk = 1) {
-    const int64_t g = kXcd * (chunk > 0 ? chunk : 1);
-    return (blocks + g - 1) / g * g;
-}
+inline int64_t xcd_chunk(int64_t blocks) { return (blocks + kXcd - 1) / kXcd; }
+inline int64_t xcd_launch(int64_t blocks) { return kXcd * xcd_chunk(blocks); }
 
 // ---------------------------------------------------------------- steady state
 // Distance of a converging field to its steady state, estimated from the decay of the

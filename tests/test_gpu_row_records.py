@@ -1,0 +1,39 @@
+"""The flow sweep finds a node's sources through one record per neighbouring row: rows that
+end inside a 32-voxel half segment, at its end and at a segment's end, rows shorter than a
+half, and lanes that stand at both ends of a half at once (nx = 33), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1410_1921_amd.workloads as W
+from paper_1410_1921_amd import lbm
+
+pytestmark = pytest.mark.gpu
+
+W19 = np.array([1 / 3] + [1 / 18] * 6 + [1 / 36] * 12)
+
+
+@pytest.mark.parametrize("pressure", [None, (1.0005, 0.9995)])
+@pytest.mark.parametrize("nx", [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 130])
+def test_row_ends(orc, nx, pressure):
+    m = W.random_mask((4, 7, nx), 0.7, nx)
+    m[0, 0, :] = 1  # one row open through both x faces
+    g = torch.from_numpy(m).cuda()
+    kw = dict(tau=0.8, force=(1e-5, 2e-6, -3e-6), fixed_steps=60, check_every=20)
+    o = orc.flow_solve(m, pressure=pressure, **kw)
+    vox = np.flatnonzero(m.reshape(-1))
+    fo = o["f"].reshape(-1, 19)[vox] - W19
+    # two steps past a check as well: the sweep that moves to new references
+    for storage, bar in ((lbm.LBM_STORE_FP64, 1e-12), (lbm.LBM_STORE_FP32, 5e-5 * np.abs(fo).max())):
+        r = lbm.lbm_flow_solve(g, pressure=pressure, storage=storage, want_u=True, **kw)
+        f, flag = lbm.lbm_flow_sample(r.workspace, vox)
+        assert flag.all()
+        assert np.abs(f - fo).max() <= bar
+        w = lbm.lbm_flow_solve(g, pressure=pressure, storage=storage, want_u=True,
+                               variant=lbm.LBM_VARIANT_OFF64, **kw)
+        assert torch.equal(w.field, r.field)
+        u = r.field.cpu().numpy().astype(np.float64)
+        assert np.abs(u - o["u"]).max() <= 1e-5 * np.abs(o["u"]).max()
+    if pressure is None:
+        _, _, us, _ = lbm.lbm_flow_solve_batch([g, g], want_u=True, group_bytes=-1, **kw)
+        assert torch.equal(us[1], r.field)
