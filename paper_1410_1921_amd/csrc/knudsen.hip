@@ -66,6 +66,19 @@ struct Shift {
     float t0, tm, tp, pad;
 };
 
+// Resident sweeps (k_resident7): one workgroup per CU at most, each with up to kResNpt nodes
+// for each of up to kResThreads threads, up to kResLinks links a thread to nodes of other
+// workgroups, and kResSenders threads more that send up to kResSends populations each.
+constexpr int kResGroups = 256;
+constexpr int kResThreads = 832;
+constexpr int kResSenders = 192;
+constexpr int kResNpt = 5;
+constexpr int kResLinks = 12;
+constexpr int kResSends = 32;
+constexpr int64_t kResNodes = (int64_t)kResGroups * kResThreads * kResNpt;
+constexpr int64_t kResSlots = (int64_t)kResGroups * kResThreads * kResLinks;
+constexpr int kResOut = kResSenders * kResSends;
+
 struct KnWs {
     KnHeader *hdr;
     unsigned long long *counter;
@@ -84,6 +97,9 @@ struct KnWs {
     double *ref[2];    // the two reference profiles, index x + 1 for x = -1..nx
     Shift *steady[2];  // shifts within each frame (t0 = 0)
     Shift *trans;      // shifts from the current frame to the other one
+    uint64_t *halo;    // packets of the resident sweeps [2][kResSlots]
+    uint2 *sends;      // their send lists [kResGroups][kResOut]
+    int *abort;        // set by a resident sweep that gave up
     double *part;      // plane-mean partial sums [nx][kPlaneParts][2]
     double *fpart;     // link-plane flux partial sums [nx + 1][kPlaneParts]
     int64_t stride;
@@ -110,7 +126,12 @@ static KnWs carve_kn(void *base, const Grid &g, int64_t nf, int q) {
     w.total = c.take<int32_t>(1);
     w.rank = c.take<RankWord>(g.nsegs());
     w.samp_vox = c.take<int64_t>(kKnSampleMax);
-    w.samp_out = c.take<double>((size_t)kKnSampleMax * 20);
+    // the packets of the resident sweeps and the samples are never held at once
+    w.halo = c.take<uint64_t>(2 * (size_t)kResSlots);
+    w.samp_out = reinterpret_cast<double *>(w.halo);
+    static_assert(2 * kResSlots >= (int64_t)kKnSampleMax * 20, "the samples fit the packets");
+    w.sends = c.take<uint2>((size_t)kResGroups * kResOut);
+    w.abort = c.take<int>(1);
     w.samp_flag = c.take<uint8_t>(kKnSampleMax);
     for (int f = 0; f < 2; f++) w.ref[f] = c.take<double>(kMaxEdge + 2);
     for (int f = 0; f < 2; f++) w.steady[f] = c.take<Shift>(kMaxEdge + 2);
@@ -150,7 +171,14 @@ struct Sweep7 {
     float *__restrict__ csnap;
     float *__restrict__ c_out;
     double *__restrict__ partials;
+    const int *__restrict__ skip;      // nullable: nothing is done when it holds non-zero (the
+                                       // resident sweep before this check gave up)
 };
+
+// The relaxation of one population: a - om (a - w C), rounded alike wherever it is formed.
+__device__ inline float relax(float a, float om, float w, float c) {
+    return __builtin_fmaf(-om, __builtin_fmaf(-w, c, a), a);
+}
 
 // The update of fluid node n at (x, y, z) with its 6 pull sources resolved: ids[i] is the
 // node at x - e_i, -1 when that voxel is solid (bounce back), -2 beyond an x face (ghost
@@ -187,7 +215,7 @@ __device__ inline void node7(const Sweep7 &a, int64_t n, int x, int y, int z, co
 #pragma unroll
     for (int i = 0; i < 7; i++) {
         const float w = i == 0 ? kW0 : kW1;
-        so[i] = ai[i] - om * (ai[i] - w * cdev);
+        so[i] = relax(ai[i], om, w, cdev);
         if (NT)
             __builtin_nontemporal_store(so[i], &a.dst[popq(7, i, n)]);
         else
@@ -222,13 +250,15 @@ __device__ inline void write_partials7(double (&acc)[NV], int64_t row, bool vali
 // in the list, in x order, so the node at x - 1 (x + 1), when fluid, is n - 1 (n + 1):
 // the entry's coordinates tell, loaded from the cache lines of n's own; the four sources
 // in the neighbouring rows come from the rank map.
-template <bool CHECK, bool NT, class Off>
-__device__ inline void sweep7_node(const Sweep7 &a, int64_t n, double (&acc)[kKnSums]) {
-    const uint32_t c = a.coords[n];
-    const uint32_t cm = n > 0 ? a.coords[n - 1] : 0xffffffffu;
-    const uint32_t cp = n + 1 < a.nf ? a.coords[n + 1] : 0xffffffffu;
-    const int x = c & 1023, y = (c >> 10) & 1023, z = c >> 20;
-    const Grid &g = a.g;
+__device__ inline void sources7(const Grid &g, const uint32_t *__restrict__ coords,
+                                const RankWord *__restrict__ rank, int64_t nf, int64_t n, int &x,
+                                int &y, int &z, int (&ids)[7]) {
+    const uint32_t c = coords[n];
+    const uint32_t cm = n > 0 ? coords[n - 1] : 0xffffffffu;
+    const uint32_t cp = n + 1 < nf ? coords[n + 1] : 0xffffffffu;
+    x = c & 1023;
+    y = (c >> 10) & 1023;
+    z = c >> 20;
     const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
     const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
     // rows of the sources 3..6 (source x - e_i)
@@ -236,26 +266,319 @@ __device__ inline void sweep7_node(const Sweep7 &a, int64_t n, double (&acc)[kKn
     const int nzs[7] = {z, z, z, z, z, zm, zp};
     RankWord rw[7];
 #pragma unroll
-    for (int i = 3; i < 7; i++) rw[i] = a.rank[g.seg(x, nys[i], nzs[i])];
-    int ids[7];
+    for (int i = 3; i < 7; i++) rw[i] = rank[g.seg(x, nys[i], nzs[i])];
     ids[0] = 0;
     // beyond an x face the source is the ghost plane (-2)
     ids[1] = x == 0 ? -2 : (cm == pack_xyz(x - 1, y, z) ? (int)(n - 1) : -1);
     ids[2] = x == g.nx - 1 ? -2 : (cp == pack_xyz(x + 1, y, z) ? (int)(n + 1) : -1);
 #pragma unroll
     for (int i = 3; i < 7; i++) ids[i] = rank_lookup(rw[i], x & (kSeg - 1));
+}
+
+template <bool CHECK, bool NT, class Off>
+__device__ inline void sweep7_node(const Sweep7 &a, int64_t n, double (&acc)[kKnSums]) {
+    int x, y, z, ids[7];
+    sources7(a.g, a.coords, a.rank, a.nf, n, x, y, z, ids);
     node7<CHECK, NT, Off>(a, n, x, y, z, ids, acc);
 }
 
 // One step, one fluid node per thread.
 template <bool CHECK, bool NT, class Off>
 __global__ __launch_bounds__(256) void k_sweep7(Sweep7 a) {
+    if (CHECK && a.skip && *a.skip) return;
     const int64_t lb = a.chunk ? xcd_block(blockIdx.x, (uint32_t)a.chunk) : (int64_t)blockIdx.x;
     const int64_t n = lb * 256 + threadIdx.x;
     double acc[kKnSums] = {0, 0, 0, 0, 0};
     if (n < a.nf) sweep7_node<CHECK, NT, Off>(a, n, acc);
     if (CHECK) write_partials7<kKnSums>(acc, lb, lb * 256 < a.nf, a.partials);
 }
+
+// ---------------------------------------------------------------- resident sweeps
+// Many steps of a lattice that fits the chip, in one launch: each workgroup (one per CU)
+// owns a run of nodes, keeps its rest populations in registers and its moving ones in LDS,
+// and exchanges with other workgroups only the populations that cross between them (2300
+// of its 19700 at 128^3).  A sweep per launch moves all 50 MB of a 128^3 lattice through
+// the Infinity Cache; here a step moves 10 MB of packets and is bound by their way from a
+// store on one XCD to a load on another.
+//
+// A packet is one 64-bit word, the population and the number of the step it belongs to,
+// stored and loaded as one atomic: a receiver polls the word itself, and needs no fence and
+// no flag.  Two sets of slots in turn are enough: a workgroup sends step t + 2 after it
+// has received every packet of step t + 1, which its neighbour sent after all its waves had
+// taken the packets of step t (links go both ways).  Sending is the work of waves of their
+// own: a wave that polls waits for its earlier stores as well, and a store takes 2.5 us to
+// be acknowledged.  While packets are on their way a workgroup works on its groups of 64
+// nodes without links, and it sends those of the others before it writes theirs.
+//
+// Per step, setup and the two plain sweeps of a check interval of 100 included: 128^3
+// (839 k nodes) 10.4 -> 4.8 us, of which 3.1 without the wait for packets (7.1 when every
+// wave sent its own packets, 5.6 before the work was put under their flight; 9.7 with
+// neighbouring workgroups on one XCD); 64^3 3.7 -> 2.5, 32^3 2.9 -> 2.2.
+//
+// Every wait is bounded: a thread that waits longer than `limit` ticks (or sees another
+// one give up) sets *abort, its workgroup leaves at its next barrier, and so do the others
+// in their waits; the state read, src, is untouched and the caller runs plain sweeps from
+// it instead.  The launch is cooperative, so all workgroups are on the chip together.
+struct Res7 {
+    Grid g;
+    int64_t nf, stride;
+    const uint32_t *__restrict__ coords;
+    const RankWord *__restrict__ rank;
+    const float *__restrict__ omega;
+    const float *__restrict__ src;
+    float *__restrict__ dst;
+    const Shift *__restrict__ shift;  // steady (t0 = 0)
+    uint64_t *halo;
+    uint2 *sends;
+    int *abort;
+    uint32_t *slots;  // k_res_slots: [6][stride], the packet slot of a pull (in dst)
+    int threads, steps;
+    uint32_t tag0;
+    uint64_t limit;
+};
+
+// The sources of the thread's nodes: remote(r, j, i, id, n) for the r-th link, population i
+// of its j-th node n pulled from node id of another workgroup, local(j, i, id, x) for the
+// others.  Both kernels below see the links in the same order.
+template <int NPT, class Local, class Remote>
+__device__ inline int resident_links(const Res7 &a, int64_t lo, int64_t hi, Local &&local,
+                                     Remote &&remote) {
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < NPT; j++) {
+        const int64_t n = lo + j * a.threads + threadIdx.x;
+        int x = 0, y = 0, z = 0, ids[7] = {0, -2, -2, -2, -2, -2, -2};
+        if (n < hi) sources7(a.g, a.coords, a.rank, a.nf, n, x, y, z, ids);
+#pragma unroll
+        for (int i = 1; i < 7; i++) {
+            if (ids[i] >= 0 && (ids[i] < lo || ids[i] >= hi)) remote(cnt++, j, i, ids[i], n);
+            else local(j, i, ids[i], x);
+        }
+        asm volatile("" ::: "memory");  // one node's lookups at a time: registers
+    }
+    return cnt;
+}
+
+// The slot of each pull from another workgroup, for the workgroup that sends it.  More
+// links than a thread has slots for, or a workgroup than its senders take (it sends as many
+// populations as it pulls), give the resident sweep up before it starts.
+template <int NPT>
+__global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a) {
+    __shared__ int total;
+    const int bd = a.threads;
+    const int64_t lo = (int64_t)blockIdx.x * NPT * bd;
+    const int64_t hi = lo + NPT * bd < a.nf ? lo + NPT * bd : a.nf;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    const int cnt = resident_links<NPT>(
+        a, lo, hi, [](int, int, int, int) {},
+        [&](int r, int, int i, int, int64_t n) {
+            if (r < kResLinks)
+                a.slots[(i - 1) * a.stride + n] = ((uint32_t)blockIdx.x * kResLinks + r) * bd + threadIdx.x;
+        });
+    atomicAdd(&total, cnt);
+    __syncthreads();
+    if (cnt > kResLinks || total > kResOut)
+        __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int NPT>
+__global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a) {
+    LBM_D3Q7_TABLES
+    constexpr int S = __HIP_MEMORY_SCOPE_AGENT;
+    __shared__ float lds[(6 * NPT + kResLinks) * kResThreads + 1];
+    __shared__ int quit, total;
+    const int bd = a.threads, tid = threadIdx.x, L = NPT * bd;
+    const int64_t lo = (int64_t)blockIdx.x * L, hi = lo + L < a.nf ? lo + L : a.nf;
+    // population i of local node l at (i - 1) L + l, the thread's packets at 6 L + r bd +
+    // tid, and a zero (the deviation of a ghost plane)
+    const int in0 = 6 * L + tid, zero = (6 * NPT + kResLinks) * bd;
+    if (tid == 0) {
+        quit = total = 0;
+        lds[zero] = 0.f;
+    }
+    __syncthreads();
+    uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
+    if (tid >= bd) {  // uniform per wave: the senders
+        __syncthreads();  // the lists are complete
+        const int q = tid - bd, n = total;
+        uint32_t from[kResSends], to[kResSends];
+#pragma unroll
+        for (int e = 0; e < kResSends; e++) {
+            const uint2 w = e * kResSenders + q < n ? sends[e * kResSenders + q] : uint2{0u, 0u};
+            from[e] = w.x;
+            to[e] = min(w.y, (uint32_t)kResSlots - 1u);
+        }
+        for (int t = 0; t < a.steps; t++) {
+            __syncthreads();  // every source is read
+            if (quit) return;
+            __syncthreads();  // the new populations of nodes with links are in place
+            if (t + 1 < a.steps) {
+                const uint64_t tag = (uint64_t)(a.tag0 + (uint32_t)t) << 32;
+                uint64_t *__restrict__ halo = a.halo + (t & 1) * kResSlots;
+#pragma unroll
+                for (int e = 0; e < kResSends; e++)
+                    if (e * kResSenders + q < n)
+                        __hip_atomic_store(&halo[to[e]], tag | __float_as_uint(lds[from[e]]),
+                                           __ATOMIC_RELAXED, S);
+            }
+            __syncthreads();  // all new populations are in place
+        }
+        return;
+    }
+    float rest[NPT], om[NPT], c1[NPT], c2[NPT];
+    uint32_t code[NPT][3];  // LDS index of each pull source, two to a word
+#pragma unroll
+    for (int j = 0; j < NPT; j++) {
+        code[j][0] = code[j][1] = code[j][2] = 0;
+        c1[j] = c2[j] = 0.f;
+    }
+    auto set_code = [&](int j, int i, int v) {
+        code[j][(i - 1) >> 1] |= (uint32_t)v << (16 * ((i - 1) & 1));
+    };
+    int linked = 0;  // bit j: the thread's node j has a link
+    const int cnt = resident_links<NPT>(
+        a, lo, hi,
+        [&](int j, int i, int id, int x) {
+            const int l = j * bd + tid;
+            set_code(j, i, id == -2 ? zero : (id == -1 ? (OPP[i] - 1) * L + l : (i - 1) * L + (int)(id - lo)));
+            // a population streamed along x from a neighbour or a ghost plane changes plane
+            if (i == 1 && id != -1 && lo + l < hi) c1[j] = a.shift[x + 1].tm;
+            if (i == 2 && id != -1 && lo + l < hi) c2[j] = a.shift[x + 1].tp;
+        },
+        [&](int r, int j, int i, int id, int64_t n) {
+            const int l = j * bd + tid;
+            set_code(j, i, in0 + r * bd);
+            linked |= 1 << j;
+            lds[in0 + r * bd] = a.src[popq(7, i, id)];  // the first step needs no packet
+            const uint32_t x = a.coords[n] & 1023u;
+            if (i == 1) c1[j] = a.shift[x + 1].tm;
+            if (i == 2) c2[j] = a.shift[x + 1].tp;
+            // the same link the other way: this node's population OPP[i] goes to node id;
+            // the active lanes' entries side by side
+            const uint64_t act = __ballot(1);
+            const int rank = __popcll(act & ((1ull << (tid & 63)) - 1));
+            int base = 0;
+            if (rank == 0) base = atomicAdd(&total, __popcll(act));
+            base = __builtin_amdgcn_readfirstlane(base);
+            sends[base + rank] = uint2{(uint32_t)((OPP[i] - 1) * L + l),
+                                       a.slots[(OPP[i] - 1) * a.stride + id]};
+        });
+#pragma unroll
+    for (int j = 0; j < NPT; j++) {
+        const int l = j * bd + tid;
+        const int64_t n = lo + l;
+        rest[j] = om[j] = 0.f;
+        if (n < hi) {
+            om[j] = a.omega[n];
+            rest[j] = a.src[popq(7, 0, n)];
+#pragma unroll
+            for (int i = 1; i < 7; i++) lds[(i - 1) * L + l] = a.src[popq(7, i, n)];
+        }
+    }
+    __syncthreads();
+    // wave-uniform: node groups of the wave (64 nodes) with a link
+    int edge = 0;
+#pragma unroll
+    for (int j = 0; j < NPT; j++)
+        if (__ballot((linked >> j) & 1)) edge |= 1 << j;
+    edge = __builtin_amdgcn_readfirstlane(edge);
+    float v[NPT][6];  // sources, then the new populations
+    auto gather = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < 6; i++) v[j][i] = lds[(code[j][i >> 1] >> (16 * (i & 1))) & 0xffffu];
+    };
+    auto collide = [&](int j) {
+        const float ai[7] = {rest[j], v[j][0] + c1[j], v[j][1] + c2[j], v[j][2], v[j][3], v[j][4], v[j][5]};
+        float c = 0.f;  // C - C_ref(x)
+#pragma unroll
+        for (int i = 0; i < 7; i++) c += ai[i];
+        rest[j] = relax(ai[0], om[j], kW0, c);
+#pragma unroll
+        for (int i = 0; i < 6; i++) v[j][i] = relax(ai[i + 1], om[j], kW1, c);
+    };
+    auto put = [&](int j) {
+        const int l = j * bd + tid;
+        if (lo + l < hi)
+#pragma unroll
+            for (int i = 0; i < 6; i++) lds[i * L + l] = v[j][i];
+    };
+    const uint32_t in_slot = ((uint32_t)blockIdx.x * kResLinks) * bd + tid;
+    for (int t = 0; t < a.steps; t++) {
+        // while the packets of the last step are on their way: the groups without links
+#pragma unroll
+        for (int j = 0; j < NPT; j++)
+            if (!((edge >> j) & 1)) {
+                gather(j);
+                collide(j);
+            }
+        if (t > 0) {
+            const uint32_t tag = a.tag0 + (uint32_t)(t - 1);
+            const uint64_t *__restrict__ halo = a.halo + ((t - 1) & 1) * kResSlots + in_slot;
+            uint64_t since = 0;
+#pragma unroll
+            for (int r0 = 0; r0 < kResLinks; r0 += 4) {  // four packets in flight
+                if (r0 >= cnt) break;
+                for (int spin = 0;; spin++) {
+                    uint64_t pk[4];
+#pragma unroll
+                    for (int r = 0; r < 4; r++)
+                        pk[r] = r0 + r < cnt ? __hip_atomic_load(&halo[(r0 + r) * bd], __ATOMIC_RELAXED, S)
+                                             : (uint64_t)tag << 32;
+                    bool all = true;
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        const bool got = (uint32_t)(pk[r] >> 32) == tag;
+                        if (got && r0 + r < cnt) lds[in0 + (r0 + r) * bd] = __uint_as_float((uint32_t)pk[r]);
+                        all = all && got;
+                    }
+                    if (all) break;
+                    if ((spin & 15) == 15) {
+                        const uint64_t now = wall_clock64();
+                        if (since == 0) since = now;
+                        if (now - since > a.limit) __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, S);
+                        if (__hip_atomic_load(a.abort, __ATOMIC_RELAXED, S)) {
+                            quit = 1;
+                            break;
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NPT; j++)
+            if ((edge >> j) & 1) gather(j);
+        __syncthreads();  // every source is read
+        if (quit) return;
+#pragma unroll
+        for (int j = 0; j < NPT; j++)
+            if ((edge >> j) & 1) {
+                collide(j);
+                put(j);
+            }
+        __syncthreads();  // the new populations of nodes with links are in place
+#pragma unroll
+        for (int j = 0; j < NPT; j++)
+            if (!((edge >> j) & 1)) put(j);
+        __syncthreads();  // all new populations are in place
+    }
+#pragma unroll
+    for (int j = 0; j < NPT; j++) {
+        const int l = j * bd + tid;
+        const int64_t n = lo + l;
+        if (n >= hi) continue;
+        a.dst[popq(7, 0, n)] = rest[j];
+#pragma unroll
+        for (int i = 1; i < 7; i++) a.dst[popq(7, i, n)] = lds[(i - 1) * L + l];
+    }
+}
+
+// Clears the step numbers of the packets a solve uses, in both sets.
+__global__ __launch_bounds__(256) void k_res_clear(uint64_t *__restrict__ halo, int64_t used) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * used; i += (int64_t)gridDim.x * 256)
+        halo[i < used ? i : kResSlots + (i - used)] = 0;
+}
+__global__ void k_res_flag(int *abort) { *abort = 0; }
 
 // ---------------------------------------------------------------- D3Q19 diffusion
 // The same update on the paper's D3Q19 lattice (Section 3.2): 18 pull sources through the
@@ -752,11 +1075,117 @@ static void launch7(const Sweep7 &a, const Variant7 &m, int32_t lattice, hipStre
     else launch7o<CHECK, uint32_t>(a, m, lattice, s);
 }
 
+// Resident sweeps of one solve.
+struct ResPlan {
+    bool on = false;
+    int npt = 1, threads = 64, groups = 1;
+    uint32_t tag = 1;    // step numbers used so far in the packets, plus one
+    int cur = 0;         // buffer and steps of the last resident launch: what is run again
+    int64_t steps = 0;   // with plain sweeps when it gave up
+};
+
+// Longest wait for a packet: 0.2 s of the 100 MHz clock (a step takes microseconds; work
+// of other streams may hold a CU back for a while).
+constexpr uint64_t kResLimit = 20000000;
+// A launch pays for its setup (rank lookups, filling and emptying the LDS: the time of
+// about three plain sweeps).
+constexpr int64_t kResMinSteps = 8;
+
+// The resident sweeps are used where the whole lattice fits one workgroup per CU and the
+// caller left the variant to the library; nodes are spread over all the CUs, at least 256
+// to a workgroup (below that the packets outweigh the nodes).
+static lbm_status resident_plan(int64_t nf, int32_t variant, int32_t lattice, ResPlan &r) {
+    r = ResPlan();
+    if (variant != 0 || lattice != LBM_LATTICE_D3Q7 || nf > kResNodes) return LBM_OK;
+    int dev = 0, cus = 0, coop = 0;
+    LBM_TRY_HIP(hipGetDevice(&dev));
+    LBM_TRY_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    LBM_TRY_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
+    if (!coop || cus < 1) return LBM_OK;
+    const int64_t groups = std::min<int64_t>(cus, kResGroups);
+    const int64_t per = std::max<int64_t>((nf + groups - 1) / groups, 256);
+    r.npt = (int)((per + kResThreads - 1) / kResThreads);
+    if (r.npt > kResNpt) return LBM_OK;
+    r.threads = (int)((per + r.npt - 1) / r.npt + 63) / 64 * 64;
+    r.groups = (int)((nf + (int64_t)r.npt * r.threads - 1) / ((int64_t)r.npt * r.threads));
+    r.on = true;
+    return LBM_OK;
+}
+
+static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift *steady, int cur,
+                          const ResPlan &r) {
+    Res7 a;
+    a.g = g;
+    a.nf = nf;
+    a.stride = w.stride;
+    a.coords = w.coords;
+    a.rank = w.rank;
+    a.omega = w.omega;
+    a.src = w.g[cur];
+    a.dst = w.g[cur ^ 1];
+    a.shift = steady;
+    a.halo = w.halo;
+    a.sends = w.sends;
+    a.abort = w.abort;
+    a.slots = reinterpret_cast<uint32_t *>(w.g[cur ^ 1]);  // 6 of its 7 arrays, until the end
+    a.threads = r.threads;
+    a.steps = 0;
+    a.tag0 = r.tag;
+    a.limit = kResLimit;
+    return a;
+}
+
+static lbm_status resident_slots(const Res7 &a, const ResPlan &r, hipStream_t s) {
+    const unsigned nb = (unsigned)r.groups, nt = (unsigned)r.threads;
+    switch (r.npt) {
+    case 1: k_res_slots<1><<<nb, nt, 0, s>>>(a); break;
+    case 2: k_res_slots<2><<<nb, nt, 0, s>>>(a); break;
+    case 3: k_res_slots<3><<<nb, nt, 0, s>>>(a); break;
+    case 4: k_res_slots<4><<<nb, nt, 0, s>>>(a); break;
+    default: k_res_slots<5><<<nb, nt, 0, s>>>(a); break;
+    }
+    LBM_CHECK_LAUNCH();
+    return LBM_OK;
+}
+
+// Whether the lattice's links fit the resident sweeps goes to *w.abort (0: they do), for
+// the caller to read at its next synchronisation; `cur` holds the state.
+static lbm_status resident_probe(const KnWs &w, const Grid &g, int64_t nf, int cur, const ResPlan &r,
+                                 hipStream_t s) {
+    k_res_flag<<<1, 1, 0, s>>>(w.abort);
+    LBM_CHECK_LAUNCH();
+    k_res_clear<<<512, 256, 0, s>>>(w.halo, (int64_t)r.groups * r.threads * kResLinks);
+    LBM_CHECK_LAUNCH();
+    return resident_slots(resident_args(w, g, nf, nullptr, cur, r), r, s);
+}
+
+// `steps` resident sweeps in the frame of `steady` from buffer cur to the other one.
+static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const Shift *steady, int cur,
+                                 int64_t steps, ResPlan &r, hipStream_t s) {
+    Res7 a = resident_args(w, g, nf, steady, cur, r);
+    a.steps = (int)steps;
+    r.tag += (uint32_t)steps;
+    r.cur = cur;
+    r.steps = steps;
+    const lbm_status st = resident_slots(a, r, s);
+    if (st != LBM_OK) return st;
+    const void *kernel = r.npt == 1   ? reinterpret_cast<const void *>(&k_resident7<1>)
+                         : r.npt == 2 ? reinterpret_cast<const void *>(&k_resident7<2>)
+                         : r.npt == 3 ? reinterpret_cast<const void *>(&k_resident7<3>)
+                         : r.npt == 4 ? reinterpret_cast<const void *>(&k_resident7<4>)
+                                      : reinterpret_cast<const void *>(&k_resident7<5>);
+    void *args[] = {&a};
+    LBM_TRY_HIP(hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
+                                           dim3((unsigned)(r.threads + kResSenders)), args, 0, s));
+    return LBM_OK;
+}
+
 // `steps` sweeps; the first one moves the state into the pending frame if there is one.
 static lbm_status kn_launch(const KnWs &w, const Grid &g, int64_t nf, KnHeader &h,
                             const Variant7 &m, int &cur, bool &pending, int64_t steps,
-                            bool check_last, float *c_field, hipStream_t s) {
+                            bool check_last, float *c_field, ResPlan *res, hipStream_t s) {
     Sweep7 a;
+    a.skip = nullptr;
     a.g = g;
     a.nf = nf;
     a.stride = w.stride;
@@ -769,6 +1198,16 @@ static lbm_status kn_launch(const KnWs &w, const Grid &g, int64_t nf, KnHeader &
     a.c_out = c_field;
     a.partials = w.partials;
     for (int64_t t = 0; t < steps; t++) {
+        // between the sweep that enters a frame and the one that checks: one launch
+        const int64_t plain = steps - t - (check_last ? 1 : 0);
+        if (res && res->on && !pending && plain >= kResMinSteps) {
+            const lbm_status st = resident_steps(w, g, nf, w.steady[h.frame], cur, plain, *res, s);
+            if (st != LBM_OK) return st;
+            a.skip = w.abort;
+            cur ^= 1;
+            t += plain - 1;
+            continue;
+        }
         if (pending) {
             a.shift = w.trans;
             h.frame ^= 1;
@@ -929,11 +1368,21 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
     }
     st = reduce_partials(w.partials, kn_blocks(nf), 1, w.res + 8, s);
     if (st != LBM_OK) return st;
+    ResPlan res;
+    st = resident_plan(nf, p->variant, h.lattice, res);
+    if (st != LBM_OK) return st;
+    int too_many = 0;
+    if (res.on) {
+        st = resident_probe(w, g, nf, cur, res, s);
+        if (st != LBM_OK) return st;
+        LBM_TRY_HIP(hipMemcpyAsync(&too_many, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+    }
     unsigned long long bad = 0;
     double sum_tau = 0.0;
     LBM_TRY_HIP(hipMemcpyAsync(&bad, w.counter, sizeof(bad), hipMemcpyDeviceToHost, s));
     LBM_TRY_HIP(hipMemcpyAsync(&sum_tau, w.res + 8, sizeof(double), hipMemcpyDeviceToHost, s));
     LBM_TRY_HIP(hipStreamSynchronize(s));
+    if (too_many) res.on = false;
     LBM_REQUIRE(bad == 0, LBM_E_INVAL, "%llu fluid nodes have tau_g <= 1/2 (pore diameter <= 0)", bad);
     if (c_field) LBM_TRY_HIP(hipMemsetAsync(c_field, 0, sizeof(float) * g.nvox(), s));
 
@@ -951,7 +1400,7 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
             if (p) (void)hipHostFree(p);
         }
     } pin;
-    LBM_TRY_HIP(hipHostMalloc((void **)&pin.p, sizeof(double) * kKnSums, hipHostMallocDefault));
+    LBM_TRY_HIP(hipHostMalloc((void **)&pin.p, sizeof(double) * (kKnSums + 1), hipHostMallocDefault));
     LBM_TRY_HIP(hipEventCreateWithFlags(&pin.got, hipEventDisableTiming));
     LBM_TRY_HIP(hipEventCreate(&pin.e0));
     LBM_TRY_HIP(hipEventCreate(&pin.e1));
@@ -970,17 +1419,31 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
         int64_t chunk = nc - (abs_t % nc);
         if (chunk > limit - t) chunk = limit - t;
         LBM_TRY_HIP(hipEventRecord(e0, s));
-        out = kn_launch(w, g, nf, h, mode, cur, pending, chunk, true, c_field, s);
+        int *const gave_up = reinterpret_cast<int *>(pin.p + kKnSums);
+        *gave_up = 0;
+        out = kn_launch(w, g, nf, h, mode, cur, pending, chunk, true, c_field, &res, s);
+        for (;;) {
+            if (out != LBM_OK) break;
+            LBM_TRY_HIP(hipEventRecord(e1, s));
+            out = reduce_partials(w.partials, kn_blocks(nf), kKnSums, w.res, s);
+            if (out != LBM_OK) break;
+            LBM_TRY_HIP(hipMemcpyAsync(pin.p, w.res, sizeof(sums), hipMemcpyDeviceToHost, s));
+            if (res.on)
+                LBM_TRY_HIP(hipMemcpyAsync(gave_up, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+            LBM_TRY_HIP(hipEventRecord(pin.got, s));
+            out = kn_next_frame(w, g, h, s);
+            if (out != LBM_OK) break;
+            pending = true;
+            LBM_TRY_HIP(hipEventSynchronize(pin.got));
+            if (!res.on || !*gave_up) break;
+            // the resident sweep gave up: its start, the frame and the snapshot are as they
+            // were (the check did nothing), so plain sweeps run its steps and the check
+            res.on = false;
+            cur = res.cur;
+            pending = false;
+            out = kn_launch(w, g, nf, h, mode, cur, pending, res.steps + 1, true, c_field, &res, s);
+        }
         if (out != LBM_OK) break;
-        LBM_TRY_HIP(hipEventRecord(e1, s));
-        out = reduce_partials(w.partials, kn_blocks(nf), kKnSums, w.res, s);
-        if (out != LBM_OK) break;
-        LBM_TRY_HIP(hipMemcpyAsync(pin.p, w.res, sizeof(sums), hipMemcpyDeviceToHost, s));
-        LBM_TRY_HIP(hipEventRecord(pin.got, s));
-        out = kn_next_frame(w, g, h, s);
-        if (out != LBM_OK) break;
-        pending = true;
-        LBM_TRY_HIP(hipEventSynchronize(pin.got));
         std::memcpy(sums, pin.p, sizeof(sums));
         float ms = 0.f;
         LBM_TRY_HIP(hipEventElapsedTime(&ms, e0, e1));
@@ -1063,7 +1526,7 @@ extern "C" lbm_status lbm_knudsen_step(void *workspace, size_t ws_bytes, int64_t
     int cur = h.cur;
     bool pending = false;
     st = kn_launch(w, g, h.n_fluid, h, pick_variant7(h.variant, w.stride, kn_q(h.lattice)), cur,
-                   pending, steps, false, nullptr, s);
+                   pending, steps, false, nullptr, nullptr, s);
     if (st != LBM_OK) return st;
     h.cur = cur;
     h.steps_done += steps;
@@ -1384,7 +1847,7 @@ extern "C" lbm_status lbm_knudsen_solve_batch(int32_t count, const int32_t *n_h,
     if (st != LBM_OK) return st;
     q.pending = true;
 
-    Sweep7 a{};
+    Sweep7 a{};  // skip: null
     a.stride = w.stride;
     a.coords = w.coords;
     a.rank = w.rank;
