@@ -99,69 +99,153 @@ __global__ __launch_bounds__(256) void k_conv3d(NnGrid g, const uint16_t *__rest
     }
 }
 
-// The same convolution on grids whose three sizes are multiples of 4: one wave per brick
-// of 4 x 4 x 4 voxels (blockIdx.x, x fastest) and block of 16 output channels
-// (blockIdx.y), the brick's four z planes of 16 voxels as four output tiles that share
-// each weight load.  Per block of 16 input channels the wave copies the 6 x 6 x 6 halo of
-// x around its brick (zero outside the grid) into LDS as loaded, voxel-major, and reads
-// each tap's shifted operand from there.
-__global__ __launch_bounds__(64) void k_conv3d_bricks(NnGrid g, const uint16_t *__restrict__ x, int x_cs,
-                                                      int cin, const uint16_t *__restrict__ w,
-                                                      int cout, const float *__restrict__ bias,
-                                                      uint16_t *__restrict__ y, int y_cs, int relu,
-                                                      int flip) {
-    __shared__ __align__(16) uint16_t sx[216 * 16];  // [halo voxel][channel]
-    const int lane = threadIdx.x, r = lane & 15, q = lane >> 4;
-    const int bx = g.nx / 4, by = g.ny / 4;
-    const int64_t b = blockIdx.x;
-    const int nb = blockIdx.y;
-    const int x0 = 4 * (int)(b % bx), y0 = 4 * (int)((b / bx) % by), z0 = 4 * (int)(b / ((int64_t)bx * by));
-    f32x4 acc[4];
+// The same convolution on grids whose three sizes are multiples of 4: a workgroup of
+// WX x WY x WZ = 4 waves, one block of 16 output channels, and a brick of 4 WX x 4 WY x
+// PZ WZ voxels, of which each wave holds a column of PZ planes of 4 x 4.  Per block of 16
+// input channels the workgroup copies its halo of x (zero outside the grid) and the block's
+// 27 x 16 x 16 weights into LDS, with 16-byte loads issued during the previous block's
+// products.
+//
+// What would bound it is the LDS operand read: 8 bytes a lane are 4 cycles of the unit that
+// four matrix cores share, a product 16 cycles of one of them.  So a wave keeps the 27
+// weights in registers and walks the input planes of its column in the order of the taps'
+// z: each of a plane's nine shifted operands is read once and multiplied into the three
+// output planes it touches, 9 (PZ + 2) reads for 27 PZ products.  The reads are free of
+// conflicts: the four channel quads lie in planes of their own, 8 bytes a voxel, rows padded
+// to 12 voxels, which puts the 16 voxels of a tile into 16 different pairs of banks.  The
+// weights are the A operand, so that a lane ends with four channels of one voxel and writes
+// them with one 8-byte store.  Every output adds its products in one order, whatever the
+// brick: input block, then tap.
+//
+// Measured, a wave per 4 x 4 x 4 brick that read both operands for every product before:
+// 96^3 x 16 -> 16 channels 50.8 -> 32.6 us, 96^3 x 48 -> 16 137 -> 69, 48^3 x 96 -> 32 83 ->
+// 39, 24^3 x 192 -> 64 73 -> 27, 12^3 x 128 -> 128 46 -> 12; 390 to 530 of the 1260 TFLOP/s
+// of the 16 x 16 x 16 products on the 96^3 levels, where what is left is a workgroup's start:
+// halo and weights are on their way while only one other workgroup of the compute unit works.
+typedef uint32_t u32x4a8 __attribute__((ext_vector_type(4), aligned(8)));  // 16 bytes at 8
+template <int WX, int WY, int WZ, int PZ, bool FLIP>
+__global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t *__restrict__ x, int x_cs,
+                                                       int cin, const uint16_t *__restrict__ w,
+                                                       int cout, const float *__restrict__ bias,
+                                                       uint16_t *__restrict__ y, int y_cs, int relu) {
+    constexpr int TX = 4 * WX, TY = 4 * WY, TZ = PZ * WZ;
+    constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, RS = 12;  // halo; row stride in voxels
+    constexpr int QS = RS * HY * HZ;                               // voxels of a quad plane
+    constexpr int NCH = HX * HY * HZ * 2;                          // 16-byte chunks of a halo
+    constexpr int PER = (NCH + 255) / 256;
+    constexpr int NWT = 27 * 32, WPER = (NWT + 255) / 256;         // 16-byte chunks of the weights
+    static_assert(WX * WY * WZ == 4 && TX <= 8, "four waves, rows of at most 10 voxels");
+    __shared__ __align__(16) uint16_t sx[4 * QS * 4];       // [quad][voxel][4 channels]
+    __shared__ __align__(16) uint16_t sw[27 * 4 * 16 * 4];  // [tap][quad][out channel][4 channels]
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bx = (g.nx + TX - 1) / TX, by = (g.ny + TY - 1) / TY;
+    const int b = (int)blockIdx.x, c0 = (int)blockIdx.y * 16;
+    const int x0 = TX * (b % bx), y0 = TY * ((b / bx) % by), z0 = TZ * (b / (bx * by));
+    // the thread's chunks of the halo: a voxel and half (8 channels) of its 16
+    int64_t src[PER];  // element offset in x, -1 outside the grid
 #pragma unroll
-    for (int sp = 0; sp < 4; sp++) acc[sp] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < cin; kc += 16) {
-        __syncthreads();  // the previous channel block's operands are read
-        for (int h = lane; h < 216; h += 64) {
-            const int sxv = x0 - 1 + h % 6, syv = y0 - 1 + (h / 6) % 6, szv = z0 - 1 + h / 36;
-            uint4 lo = uint4{0u, 0u, 0u, 0u}, hi = uint4{0u, 0u, 0u, 0u};
-            if (sxv >= 0 && sxv < g.nx && syv >= 0 && syv < g.ny && szv >= 0 && szv < g.nz) {
-                const int64_t v = ((int64_t)szv * g.ny + syv) * g.nx + sxv;
-                const uint4 *src = reinterpret_cast<const uint4 *>(x + v * x_cs + kc);
-                lo = src[0];
-                hi = src[1];
-            }
-            uint4 *dst = reinterpret_cast<uint4 *>(sx + h * 16);
-            dst[0] = lo;
-            dst[1] = hi;
+    for (int k = 0; k < PER; k++) {
+        const int c = tid + 256 * k, v = c >> 1;
+        const int vx = x0 - 1 + v % HX, vy = y0 - 1 + (v / HX) % HY, vz = z0 - 1 + v / (HX * HY);
+        src[k] = c < NCH && vx >= 0 && vx < g.nx && vy >= 0 && vy < g.ny && vz >= 0 && vz < g.nz
+                     ? (((int64_t)vz * g.ny + vy) * g.nx + vx) * x_cs + 8 * (c & 1)
+                     : -1;
+    }
+    uint4 pre[PER];
+    u32x4a8 wpre[WPER];
+    auto load_block = [&](int kc) {
+#pragma unroll
+        for (int k = 0; k < PER; k++)
+            pre[k] = src[k] >= 0 ? *reinterpret_cast<const uint4 *>(x + src[k] + kc) : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int k = 0; k < WPER; k++) {
+            const int c = tid + 256 * k;  // tap, out channel, half
+            if (c < NWT)
+                wpre[k] = *reinterpret_cast<const u32x4a8 *>(
+                    w + ((int64_t)(c >> 5) * cout + c0 + ((c >> 1) & 15)) * cin + kc + 8 * (c & 1));
         }
-        __syncthreads();
-        const uint16_t *wp = w + ((int64_t)nb * 16 + r) * cin + kc + 4 * q;
-        for (int t = 0; t < 27; t++) {
-            int dx, dy, dz;
-            tap_offset(t, flip, dx, dy, dz);
-            // B[k = 4 q .. 4 q + 3][n = r]: w[t][nb 16 + r][kc + 4 q ..]
-            const bf16x4 bw = *reinterpret_cast<const bf16x4 *>(wp + (int64_t)t * cout * cin);
+    };
+    auto store_block = [&]() {
 #pragma unroll
-            for (int sp = 0; sp < 4; sp++) {
-                // A[m = r][k = 4 q ..]: plane voxel r = (r & 3, r >> 2) of plane sp, shifted
-                const int h = (1 + (r & 3) + dx) + 6 * (1 + (r >> 2) + dy) + 36 * (1 + sp + dz);
-                const bf16x4 a = *reinterpret_cast<const bf16x4 *>(sx + h * 16 + 4 * q);
-                acc[sp] = mfma16(a, bw, acc[sp]);
+        for (int k = 0; k < PER; k++) {
+            const int c = tid + 256 * k, v = c >> 1;
+            if (c < NCH) {
+                uint16_t *d = sx + (2 * (c & 1) * QS + (v / HX) * RS + v % HX) * 4;
+                *reinterpret_cast<uint2 *>(d) = uint2{pre[k].x, pre[k].y};
+                *reinterpret_cast<uint2 *>(d + 4 * QS) = uint2{pre[k].z, pre[k].w};
             }
+        }
+#pragma unroll
+        for (int k = 0; k < WPER; k++) {
+            const int c = tid + 256 * k;
+            if (c < NWT) {
+                uint16_t *d = sw + (((c >> 5) * 4 + 2 * (c & 1)) * 16 + ((c >> 1) & 15)) * 4;
+                *reinterpret_cast<uint2 *>(d) = uint2{wpre[k].x, wpre[k].y};
+                *reinterpret_cast<uint2 *>(d + 64) = uint2{wpre[k].z, wpre[k].w};
+            }
+        }
+    };
+    const int tx = wave % WX, ty = (wave / WX) % WY, tz = wave / (WX * WY) * PZ;
+    // element offset in sx of the lane's voxel of the column's lowest input plane, quad q
+    const int base = (q * QS + (tz * HY + ty * 4 + (r >> 2) + 1) * RS + tx * 4 + (r & 3) + 1) * 4;
+    f32x4 acc[PZ];
+#pragma unroll
+    for (int p = 0; p < PZ; p++) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    load_block(0);
+    for (int kc = 0; kc < cin; kc += 16) {
+        if (kc) __syncthreads();  // the previous channel block's operands are read
+        store_block();
+        __syncthreads();
+        if (kc + 16 < cin) load_block(kc + 16);
+        bf16x4 wv[27];  // A[m = r][k = 4 q .. 4 q + 3]
+#pragma unroll
+        for (int t = 0; t < 27; t++) wv[t] = *reinterpret_cast<const bf16x4 *>(sw + (t * 64 + lane) * 4);
+#pragma unroll
+        for (int i = 0; i < PZ + 2; i++) {  // input planes, upwards, or downwards for the mirrored taps
+            const int h = FLIP ? PZ + 1 - i : i;
+            bf16x4 av[9];  // B[k = 4 q .. 4 q + 3][n = r]
+#pragma unroll
+            for (int u = 0; u < 9; u++) {
+                const int off = (FLIP ? -1 : 1) * (u % 3 - 1 + RS * (u / 3 - 1));
+                av[u] = *reinterpret_cast<const bf16x4 *>(sx + base + (h * HY * RS + off) * 4);
+            }
+#pragma unroll
+            for (int u = 0; u < 9; u++)
+#pragma unroll
+                for (int dz = 0; dz < 3; dz++) {
+                    const int p = FLIP ? h + dz - 2 : h - dz;  // the output plane of tap dz
+                    if (p >= 0 && p < PZ) acc[p] = mfma16(wv[dz * 9 + u], av[u], acc[p]);
+                }
         }
     }
-    // D[m = 4 q + j][n = r]: plane voxel (j, q) of plane sp, output channel nb 16 + r
-    const int c = nb * 16 + r;
-    const float bc = bias ? bias[c] : 0.f;
+    // D[m = 4 q + j][n = r]: output channel c0 + 4 q + j, voxel (r & 3, r >> 2) of the plane
+    const int vx = x0 + tx * 4, vy = y0 + ty * 4;
+    if (vx >= g.nx || vy >= g.ny) return;
+    const bool wide = y_cs % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+    float bc[4];
 #pragma unroll
-    for (int sp = 0; sp < 4; sp++)
+    for (int j = 0; j < 4; j++) bc[j] = bias ? bias[c0 + 4 * q + j] : 0.f;
+#pragma unroll
+    for (int p = 0; p < PZ; p++) {
+        const int vz = z0 + tz + p;
+        if (vz >= g.nz) break;
+        uint32_t o[2];
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            float v = acc[sp][j] + bc;
+            float v = acc[p][j] + bc[j];
             if (relu) v = v > 0.f ? v : 0.f;
-            const int64_t vox = ((int64_t)(z0 + sp) * g.ny + y0 + q) * g.nx + x0 + j;
-            y[vox * y_cs + c] = f2bf(v);
+            const uint32_t h = f2bf(v);
+            o[j >> 1] = j & 1 ? o[j >> 1] | h << 16 : h;
         }
+        uint16_t *d = y + (((int64_t)vz * g.ny + vy + (r >> 2)) * g.nx + vx + (r & 3)) * y_cs + c0 + 4 * q;
+        if (wide) {
+            *reinterpret_cast<uint2 *>(d) = uint2{o[0], o[1]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) d[j] = (uint16_t)(o[j >> 1] >> (j & 1) * 16);
+        }
+    }
 }
 
 // Partial weight gradients over one chunk of voxels for tap t = blockIdx.y and output
@@ -678,6 +762,41 @@ static lbm_status check_grid(const int32_t n[3], NnGrid &g) {
     return LBM_OK;
 }
 
+template <int WX, int WY, int WZ, int PZ>
+static void conv_bricks(const NnGrid &g, const uint16_t *x, int x_cs, int cin, const uint16_t *w,
+                        const float *bias, uint16_t *y, int y_cs, int cout, int relu, int flip,
+                        hipStream_t s) {
+    const auto cut = [](int n, int t) { return (unsigned)((n + t - 1) / t); };
+    const dim3 grid(cut(g.nx, 4 * WX) * cut(g.ny, 4 * WY) * cut(g.nz, PZ * WZ), (unsigned)(cout / 16));
+    if (flip)
+        k_conv3d_bricks<WX, WY, WZ, PZ, true><<<grid, 256, 0, s>>>(g, x, x_cs, cin, w, cout, bias, y, y_cs, relu);
+    else
+        k_conv3d_bricks<WX, WY, WZ, PZ, false><<<grid, 256, 0, s>>>(g, x, x_cs, cin, w, cout, bias, y, y_cs, relu);
+}
+// The brick of a layer: a longer column reads fewer operands per product and a smaller halo,
+// a smaller brick gives more workgroups where the layer leaves compute units idle.  The lines
+// lie between 324 and 432 groups of 8 x 8 x 8 (24^3 x 64 -> 192 channels: 25.6 us with those,
+// 23.4 with 8 x 8 x 4; 48^3 x 96 -> 32: 39.2 against 45.1), 216 and 648 of 8 x 8 x 4 (24^3 x
+// 192 -> 64: 27.6 against 26.7 with 8 x 4 x 4; 24^3 x 64 -> 192: 23.4 against 26.3) and 144
+// and 432 of 8 x 4 x 4 (12^3 x 128 -> 128: 13.2 against 11.9 with 4 x 4 x 4; 24^3 x 192 -> 64:
+// 26.7 against 38.2).  A column of 8 planes is taken where 8 divides nz: less than a whole
+// column of the last brick would be worked for nothing.
+static void conv_launch(const NnGrid &g, const uint16_t *x, int x_cs, int cin, const uint16_t *w,
+                        const float *bias, uint16_t *y, int y_cs, int cout, int relu, int flip,
+                        hipStream_t s) {
+    const auto groups = [&](int tx, int ty, int tz) {
+        return (int64_t)((g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty) * ((g.nz + tz - 1) / tz) * (cout / 16);
+    };
+    if (g.nz % 8 == 0 && groups(8, 8, 8) >= 384)
+        conv_bricks<2, 2, 1, 8>(g, x, x_cs, cin, w, bias, y, y_cs, cout, relu, flip, s);
+    else if (groups(8, 8, 4) >= 320)
+        conv_bricks<2, 2, 1, 4>(g, x, x_cs, cin, w, bias, y, y_cs, cout, relu, flip, s);
+    else if (groups(8, 4, 4) >= 320)
+        conv_bricks<2, 1, 2, 2>(g, x, x_cs, cin, w, bias, y, y_cs, cout, relu, flip, s);
+    else
+        conv_bricks<1, 1, 4, 1>(g, x, x_cs, cin, w, bias, y, y_cs, cout, relu, flip, s);
+}
+
 static bool aligned8(const void *p) { return ((uintptr_t)p & 7u) == 0; }
 
 static int64_t wgrad_chunk(int64_t nvox) {
@@ -717,8 +836,7 @@ extern "C" lbm_status lbm_nn_conv3d(const int32_t n[3], const uint16_t *x, int32
         LBM_REQUIRE(cout == 16 || cout == 32 || cout == 48 || cout == 64 || cout == 96 ||
                         cout == 128 || cout == 192,
                     LBM_E_INVAL, "lbm_nn_conv3d: cout %d not supported", cout);
-        k_conv3d_bricks<<<dim3((unsigned)(g.nvox / 64), (unsigned)(cout / 16)), 64, 0, s>>>(
-            g, x, x_cs, cin, w, cout, bias, y, y_cs, relu, flip);
+        conv_launch(g, x, x_cs, cin, w, bias, y, y_cs, cout, relu, flip, s);
         LBM_CHECK_LAUNCH();
         return LBM_OK;
     }
