@@ -19,6 +19,7 @@
 namespace lbm {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -34,6 +35,15 @@ __device__ inline uint16_t f2bf(float f) {
 // B[k = 4q .. 4q+3][n = r] and D[m = 4q .. 4q+3][n = r].
 __device__ inline f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// The same with K = 32: lanes hold k = 8 q .. 8 q + 7.
+__device__ inline f32x4 mfma32(bf16x8 a, bf16x8 b, f32x4 c) {
+    typedef __bf16 v8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+}
+__device__ inline bf16x8 join(bf16x4 a, bf16x4 b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 struct NnGrid {
@@ -131,8 +141,8 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     constexpr int TX = 4 * WX, TY = 4 * WY, TZ = PZ * WZ;
     constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, RS = 12;  // halo; row stride in voxels
     constexpr int QS = RS * HY * HZ;                               // voxels of a quad plane
-    constexpr int NCH = HX * HY * HZ * 2;                          // 16-byte chunks of a halo
-    constexpr int PER = (NCH + 255) / 256;
+    constexpr int NCP = HX * HY * 2, PP = 256 / NCP;  // 16-byte chunks of a halo plane; planes at once
+    constexpr int PER = (HZ + PP - 1) / PP;
     constexpr int NWT = 27 * 32, WPER = (NWT + 255) / 256;         // 16-byte chunks of the weights
     static_assert(WX * WY * WZ == 4 && TX <= 8, "four waves, rows of at most 10 voxels");
     __shared__ __align__(16) uint16_t sx[4 * QS * 4];       // [quad][voxel][4 channels]
@@ -142,22 +152,24 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     const int bx = (g.nx + TX - 1) / TX, by = (g.ny + TY - 1) / TY;
     const int b = (int)blockIdx.x, c0 = (int)blockIdx.y * 16;
     const int x0 = TX * (b % bx), y0 = TY * ((b / bx) % by), z0 = TZ * (b / (bx * by));
-    // the thread's chunks of the halo: a voxel and half (8 channels) of its 16
-    int64_t src[PER];  // element offset in x, -1 outside the grid
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const int c = tid + 256 * k, v = c >> 1;
-        const int vx = x0 - 1 + v % HX, vy = y0 - 1 + (v / HX) % HY, vz = z0 - 1 + v / (HX * HY);
-        src[k] = c < NCH && vx >= 0 && vx < g.nx && vy >= 0 && vy < g.ny && vz >= 0 && vz < g.nz
-                     ? (((int64_t)vz * g.ny + vy) * g.nx + vx) * x_cs + 8 * (c & 1)
-                     : -1;
-    }
+    // the thread's chunks of the halo: one place in the plane, half (8 channels) of its 16, in
+    // the planes hz, hz + PP, ..
+    const int hc = tid % NCP, hz = tid / NCP, hx = (hc >> 1) % HX, hy = (hc >> 1) / HX;
+    const int sxv = x0 - 1 + hx, syv = y0 - 1 + hy, szv = z0 - 1 + hz;
+    const bool inside = hz < PP && sxv >= 0 && sxv < g.nx && syv >= 0 && syv < g.ny;
+    const int64_t plane = (int64_t)g.nx * g.ny * x_cs;
+    const uint16_t *const src = x + szv * plane + ((int64_t)syv * g.nx + sxv) * x_cs + 8 * (hc & 1);
+    uint16_t *const dst = sx + (2 * (hc & 1) * QS + (hz * HY + hy) * RS + hx) * 4;
     uint4 pre[PER];
     u32x4a8 wpre[WPER];
     auto load_block = [&](int kc) {
 #pragma unroll
-        for (int k = 0; k < PER; k++)
-            pre[k] = src[k] >= 0 ? *reinterpret_cast<const uint4 *>(x + src[k] + kc) : uint4{0u, 0u, 0u, 0u};
+        for (int k = 0; k < PER; k++) {
+            const int vz = szv + PP * k;
+            pre[k] = uint4{0u, 0u, 0u, 0u};
+            if (inside && hz + PP * k < HZ && vz >= 0 && vz < g.nz)
+                pre[k] = *reinterpret_cast<const uint4 *>(src + PP * k * plane + kc);
+        }
 #pragma unroll
         for (int k = 0; k < WPER; k++) {
             const int c = tid + 256 * k;  // tap, out channel, half
@@ -169,9 +181,8 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     auto store_block = [&]() {
 #pragma unroll
         for (int k = 0; k < PER; k++) {
-            const int c = tid + 256 * k, v = c >> 1;
-            if (c < NCH) {
-                uint16_t *d = sx + (2 * (c & 1) * QS + (v / HX) * RS + v % HX) * 4;
+            if (hz < PP && hz + PP * k < HZ) {
+                uint16_t *d = dst + PP * k * HY * RS * 4;
                 *reinterpret_cast<uint2 *>(d) = uint2{pre[k].x, pre[k].y};
                 *reinterpret_cast<uint2 *>(d + 4 * QS) = uint2{pre[k].z, pre[k].w};
             }
@@ -303,117 +314,174 @@ __global__ __launch_bounds__(64) void k_conv3d_wgrad(NnGrid g, const uint16_t *_
         for (int j = 0; j < 4; j++) part_b[ch * cout + cb * 16 + 4 * q + j] = accb[j];
 }
 
-// The same weight gradient on grids whose three sizes are multiples of 4, with its
-// operands staged in LDS.  The voxels go in bricks of 4 x 4 x 4 (x fastest inside a
-// brick); one matrix-core step takes K = 16 voxels, one z plane of a brick.  A wave owns
-// one chunk of bricks (blockIdx.x), one block of 16 output channels and one of 16 input
-// channels (blockIdx.y), and all 27 taps: per brick it copies the brick's gy (64 voxels x
-// 16 channels) and the 6 x 6 x 6 halo of x around it (zero outside the grid) into LDS as
-// loaded, voxel-major, and reads each operand across voxels from there, so every tap
-// reuses one load of gy and one of x.  Partial sums as in k_conv3d_wgrad.
-__global__ __launch_bounds__(64) void k_conv3d_wgrad_bricks(NnGrid g, const uint16_t *__restrict__ x,
-                                                            int x_cs, int cin,
-                                                            const uint16_t *__restrict__ gy,
-                                                            int g_cs, int cout, int64_t bricks,
-                                                            float *__restrict__ part,
-                                                            float *__restrict__ part_b) {
-    __shared__ __align__(16) uint16_t sg[64 * 16];   // [brick voxel][channel]
-    __shared__ __align__(16) uint16_t sx[216 * 16];  // [halo voxel][channel]
-    const int lane = threadIdx.x, r = lane & 15, q = lane >> 4;
+// Four values of one channel at four consecutive voxels, out of LDS rows of 16 channels: the
+// 16 lanes of a group read a 4 x 16 block, 8 bytes each in memory order, and lane r receives
+// its column r.
+__device__ __forceinline__ bf16x4 read_column4(const uint16_t *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) bf16x4 *)p);
+}
+
+// The same weight gradient on grids whose three sizes are multiples of 4: a workgroup of four
+// waves owns one chunk of bricks of 8 x 8 x 4 voxels (blockIdx.x), one block of 16 output
+// channels and one of 16 input channels (blockIdx.y), and all 27 taps; each wave takes a
+// column of 4 x 4 x 4 of every brick (none where the brick is cut by the grid's upper x or y
+// side).  The brick's gy and the halo of x around it (zero outside the grid) are loaded
+// during the previous brick's products and go to LDS as they lie in memory, 16 channels a
+// voxel.
+//
+// A product sums over K = 32 voxels, two z planes of a column, so both operands run across
+// voxels: read_column4 turns them on their way out of LDS (2-byte reads, four for every
+// operand, were what this took its time for).  Per (dx, dy) the six input planes are read
+// once and used for all three dz, 54 reads for 54 products of 16 cycles.  The four waves'
+// sums are added through LDS at the end, in one order, so that a workgroup writes one partial
+// row.
+__global__ __launch_bounds__(256, 2) void k_conv3d_wgrad_bricks(NnGrid g, const uint16_t *__restrict__ x,
+                                                                int x_cs, int cin,
+                                                                const uint16_t *__restrict__ gy,
+                                                                int g_cs, int cout, int bricks, int nb,
+                                                                float *__restrict__ part,
+                                                                float *__restrict__ part_b) {
+    constexpr int H = 10, HN = H * H * 6;            // halo voxels in x and y, in all
+    constexpr int NCP = 2 * H * H;                   // 16-byte chunks of a halo plane
+    constexpr int SUM = 28 * 256;                    // a wave's sums: 27 taps and gy's own
+    __shared__ __align__(16) float lds[2 * SUM];
+    uint16_t *const sx = reinterpret_cast<uint16_t *>(lds), *const sg = sx + HN * 16;
+    static_assert((HN + 256) * 16 * 2 <= 2 * SUM * 4, "halo and gy lie in the sums' memory");
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wx = wave & 1, wy = wave >> 1;
     const int64_t ch = blockIdx.x;
     const int ncb = cout / 16;
     const int cb = (int)blockIdx.y % ncb, ib = (int)blockIdx.y / ncb;
-    const int bx = g.nx / 4, by = g.ny / 4, bz = g.nz / 4;
-    const int64_t nb = (int64_t)bx * by * bz;
-    const int64_t b_lo = ch * bricks;
-    const int64_t b_hi = b_lo + bricks < nb ? b_lo + bricks : nb;
-    const bool want_b = ib == 0;
-    f32x4 acc[27];
+    const int bx = (g.nx + 7) / 8, by = (g.ny + 7) / 8;
+    const int b_lo = (int)ch * bricks, b_hi = b_lo + bricks < nb ? b_lo + bricks : nb;
+    // the thread's chunks: half (8 channels) of one voxel of a plane, in each plane of the halo
+    // and in every other plane of gy
+    const int hc = tid % NCP, hx = (hc >> 1) % H - 1, hy = (hc >> 1) / H - 1;
+    const int gxv = (tid >> 1) & 7, gyv = (tid >> 4) & 7, gzv = tid >> 7;
+    const int64_t xplane = (int64_t)g.nx * g.ny * x_cs, gplane = (int64_t)g.nx * g.ny * g_cs;
+    const uint16_t *const xs = x + ((int64_t)hy * g.nx + hx) * x_cs + ib * 16 + 8 * (hc & 1);
+    const uint16_t *const gs = gy + gzv * gplane + ((int64_t)gyv * g.nx + gxv) * g_cs + cb * 16 + 8 * (tid & 1);
+    uint4 px[6], pg[2];
+    auto load_brick = [&](int x0, int y0, int z0) {
+        const int64_t o = ((int64_t)z0 * g.ny + y0) * g.nx + x0;  // the brick's first voxel
+        const bool in_g = x0 + gxv < g.nx && y0 + gyv < g.ny;
+        const bool in_x = tid < NCP && x0 + hx >= 0 && x0 + hx < g.nx && y0 + hy >= 0 && y0 + hy < g.ny;
 #pragma unroll
-    for (int t = 0; t < 27; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 accb = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 2; k++) pg[k] = uint4{0u, 0u, 0u, 0u};
+        if (in_g)
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+                pg[k] = *reinterpret_cast<const uint4 *>(gs + o * g_cs + 2 * k * gplane);
+#pragma unroll
+        for (int k = 0; k < 6; k++) px[k] = uint4{0u, 0u, 0u, 0u};
+        if (in_x) {
+#pragma unroll
+            for (int k = 0; k < 6; k++)
+                if (z0 - 1 + k >= 0 && z0 - 1 + k < g.nz)
+                    px[k] = *reinterpret_cast<const uint4 *>(xs + o * x_cs + (k - 1) * xplane);
+        }
+    };
+    f32x4 acc[28];
+#pragma unroll
+    for (int t = 0; t < 28; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const short one = (short)0x3f80;  // bfloat16 1.0
-    const bf16x4 ones = bf16x4{one, one, one, one};
-    for (int64_t b = b_lo; b < b_hi; b++) {
-        const int x0 = 4 * (int)(b % bx), y0 = 4 * (int)((b / bx) % by), z0 = 4 * (int)(b / ((int64_t)bx * by));
+    const bf16x8 ones = bf16x8{one, one, one, one, one, one, one, one};
+    // lane's address inside a 4 x 16 block: voxel r / 4 of the row, channels 4 (r % 4) ..
+    const uint16_t *const ga = sg + ((wy * 4 + q) * 8 + wx * 4 + (r >> 2)) * 16 + 4 * (r & 3);
+    const uint16_t *const xa = sx + ((wy * 4 + q + 1) * H + wx * 4 + (r >> 2) + 1) * 16 + 4 * (r & 3);
+    int x0 = 8 * (b_lo % bx), y0 = 8 * ((b_lo / bx) % by), z0 = 4 * (b_lo / (bx * by));
+    load_brick(x0, y0, z0);
+    for (int b = b_lo; b < b_hi; b++) {
+        const bool column = x0 + 4 * wx < g.nx && y0 + 4 * wy < g.ny;
         __syncthreads();  // the previous brick's operands are read
-        {
-            // lane k copies brick voxel k = x + 4 y + 16 z: 16 channels, 32 bytes
-            const int64_t v = ((int64_t)(z0 + (lane >> 4)) * g.ny + y0 + ((lane >> 2) & 3)) * g.nx +
-                              x0 + (lane & 3);
-            const uint4 *src = reinterpret_cast<const uint4 *>(gy + v * g_cs + cb * 16);
-            uint4 *dst = reinterpret_cast<uint4 *>(sg + lane * 16);
-            dst[0] = src[0];
-            dst[1] = src[1];
-        }
-        for (int h = lane; h < 216; h += 64) {
-            const int sxv = x0 - 1 + h % 6, syv = y0 - 1 + (h / 6) % 6, szv = z0 - 1 + h / 36;
-            uint4 lo = uint4{0u, 0u, 0u, 0u}, hi = uint4{0u, 0u, 0u, 0u};
-            if (sxv >= 0 && sxv < g.nx && syv >= 0 && syv < g.ny && szv >= 0 && szv < g.nz) {
-                const int64_t v = ((int64_t)szv * g.ny + syv) * g.nx + sxv;
-                const uint4 *src = reinterpret_cast<const uint4 *>(x + v * x_cs + ib * 16);
-                lo = src[0];
-                hi = src[1];
-            }
-            uint4 *dst = reinterpret_cast<uint4 *>(sx + h * 16);
-            dst[0] = lo;
-            dst[1] = hi;
-        }
+#pragma unroll
+        for (int k = 0; k < 2; k++) *reinterpret_cast<uint4 *>(sg + (tid + 256 * k) * 8) = pg[k];
+#pragma unroll
+        for (int k = 0; k < 6; k++)
+            if (tid < NCP) *reinterpret_cast<uint4 *>(sx + (tid + NCP * k) * 8) = px[k];
         __syncthreads();
-        // A[m = output channel r][k = 4 q + j] = gy at brick voxel (j, q, s) of plane s
-        bf16x4 a[4];
+        x0 += 8;
+        if (x0 >= g.nx) x0 = 0, y0 += 8;
+        if (y0 >= g.ny) y0 = 0, z0 += 4;
+        if (b + 1 < b_hi) load_brick(x0, y0, z0);
+        if (!column) continue;
+        // A[m = output channel r][k = 8 q + 4 e + j] = gy at voxel (j, q) of plane 2 i + e
+        bf16x8 a[2];
 #pragma unroll
-        for (int sp = 0; sp < 4; sp++)
+        for (int i = 0; i < 2; i++)
+            a[i] = join(read_column4(ga + 2 * i * 64 * 16), read_column4(ga + (2 * i + 1) * 64 * 16));
+        if (ib == 0)
 #pragma unroll
-            for (int j = 0; j < 4; j++) a[sp][j] = (short)sg[(16 * sp + 4 * q + j) * 16 + r];
-        if (want_b)
+            for (int i = 0; i < 2; i++) acc[27] = mfma32(a[i], ones, acc[27]);
 #pragma unroll
-            for (int sp = 0; sp < 4; sp++) accb = mfma16(a[sp], ones, accb);
+        for (int u = 0; u < 9; u++) {
+            // B[k][n = input channel r] = x at that voxel + (dx, dy, dz)
+            bf16x4 bv[6];
 #pragma unroll
-        for (int t = 0; t < 27; t++) {
-            const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
+            for (int h = 0; h < 6; h++)
+                bv[h] = read_column4(xa + (h * H * H + (u / 3 - 1) * H + u % 3 - 1) * 16);
 #pragma unroll
-            for (int sp = 0; sp < 4; sp++) {
-                // B[k = 4 q + j][n = input channel r] = x at that voxel + (dx, dy, dz)
-                bf16x4 bv;
-                const int h0 = (1 + dx) + 6 * (q + 1 + dy) + 36 * (sp + 1 + dz);
+            for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int j = 0; j < 4; j++) bv[j] = (short)sx[(h0 + j) * 16 + r];
-                acc[t] = mfma16(a[sp], bv, acc[t]);
-            }
+                for (int dz = 0; dz < 3; dz++)
+                    acc[dz * 9 + u] = mfma32(a[i], join(bv[2 * i + dz], bv[2 * i + dz + 1]), acc[dz * 9 + u]);
         }
     }
+    // the four waves' sums: waves 2 and 3 to 0 and 1, then 1 to 0
+#pragma unroll
+    for (int half = 2; half >= 1; half >>= 1) {
+        __syncthreads();
+        float *const m = lds + (wave & (half - 1)) * SUM + 4 * lane;
+        if (wave >= half && wave < 2 * half)
+#pragma unroll
+            for (int t = 0; t < 28; t++) *reinterpret_cast<f32x4 *>(m + t * 256) = acc[t];
+        __syncthreads();
+        if (wave < half)
+#pragma unroll
+            for (int t = 0; t < 28; t++) acc[t] += *reinterpret_cast<const f32x4 *>(m + t * 256);
+    }
+    if (wave) return;
 #pragma unroll
     for (int t = 0; t < 27; t++)
 #pragma unroll
         for (int j = 0; j < 4; j++)
             part[((ch * 27 + t) * cout + cb * 16 + 4 * q + j) * cin + ib * 16 + r] = acc[t][j];
-    if (want_b && r == 0)
+    if (ib == 0 && r == 0)
 #pragma unroll
-        for (int j = 0; j < 4; j++) part_b[ch * cout + cb * 16 + 4 * q + j] = accb[j];
+        for (int j = 0; j < 4; j++) part_b[ch * cout + cb * 16 + 4 * q + j] = acc[27][j];
 }
 
-// out[i] (+)= sum_c part[c * count + i] over c = 0 .. nparts - 1 in a fixed order: 16
-// threads per output each sum one contiguous sixteenth of the partials in order, then
-// the sixteen sums are added in order (256 threads: 16 outputs x 16 groups).
+// out[i] (+)= sum_c part[c * count + i] over c = 0 .. nparts - 1 for i < count, and the same
+// of part_b into out_b for the n_b outputs of the bias, which the blocks from nblk on work
+// (none: n_b = 0), in a fixed order: G threads per four outputs each sum one contiguous
+// G-th of the partials in order, then the G sums are added in order.  Count and n_b are
+// multiples of 16, so a group of four is whole; it is read with 16 bytes a lane.
+template <int G>
 __global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ part, int64_t nparts,
                                                    int64_t count, float *__restrict__ out,
+                                                   const float *__restrict__ part_b, int n_b,
+                                                   float *__restrict__ out_b, unsigned nblk,
                                                    int accumulate) {
-    __shared__ float lds[16][17];
-    const int o = threadIdx.x & 15, gr = threadIdx.x >> 4;
-    const int64_t i = (int64_t)blockIdx.x * 16 + o;
-    const int64_t per = (nparts + 15) / 16;
+    constexpr int O = 256 / G;
+    __shared__ f32x4 lds[G][O + 1];
+    unsigned blk = blockIdx.x;
+    if (blk >= nblk) blk -= nblk, part = part_b, count = n_b, out = out_b;
+    const int o = threadIdx.x % O, gr = threadIdx.x / O;
+    const int64_t i = ((int64_t)blk * O + o) * 4;
+    const int64_t per = (nparts + G - 1) / G;
     const int64_t c0 = gr * per, c1 = c0 + per < nparts ? c0 + per : nparts;
-    float s = 0.f;
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
     if (i < count)
-        for (int64_t c = c0; c < c1; c++) s += part[c * count + i];
+#pragma unroll 4
+        for (int64_t c = c0; c < c1; c++) s += *reinterpret_cast<const f32x4 *>(part + c * count + i);
     lds[gr][o] = s;
     __syncthreads();
     if (gr == 0 && i < count) {
-        float t = 0.f;
+        f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < 16; k++) t += lds[k][o];
-        out[i] = accumulate ? out[i] + t : t;
+        for (int k = 0; k < G; k++) t += lds[k][o];
+#pragma unroll
+        for (int j = 0; j < 4; j++) out[i + j] = accumulate ? out[i + j] + t[j] : t[j];
     }
 }
 
@@ -854,6 +922,19 @@ extern "C" lbm_status lbm_nn_conv3d(const int32_t n[3], const uint16_t *x, int32
     return LBM_OK;
 }
 
+// Sums of the partial rows: 16 threads an output where they are many, one where few rows or
+// many outputs keep the device busy without.
+static void sum_parts(const float *part, int64_t nparts, int64_t count, float *out, const float *part_b,
+                      int n_b, float *out_b, int accumulate, hipStream_t s) {
+    const bool wide = nparts >= 16;
+    const int64_t per = (wide ? 16 : 256) * 4;
+    const unsigned nblk = (unsigned)((count + per - 1) / per), nblk_b = (unsigned)((n_b + per - 1) / per);
+    if (wide)
+        k_sum_parts<16><<<nblk + nblk_b, 256, 0, s>>>(part, nparts, count, out, part_b, n_b, out_b, nblk, accumulate);
+    else
+        k_sum_parts<1><<<nblk + nblk_b, 256, 0, s>>>(part, nparts, count, out, part_b, n_b, out_b, nblk, accumulate);
+}
+
 extern "C" size_t lbm_nn_wgrad_workspace(const int32_t n[3], int32_t cin, int32_t cout) {
     if (!n || n[0] < 1 || n[1] < 1 || n[2] < 1 || cin < 1 || cout < 1) return 0;
     const int64_t nvox = (int64_t)n[0] * n[1] * n[2];
@@ -880,18 +961,24 @@ extern "C" lbm_status lbm_nn_conv3d_wgrad(const int32_t n[3], const uint16_t *x,
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t chunk = wgrad_chunk(g.nvox);
     int64_t nch = (g.nvox + chunk - 1) / chunk;  // the workspace's partial rows
-    float *part = static_cast<float *>(workspace);
+    // 16-byte rows inside the workspace's 256 spare bytes
+    float *part = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(workspace) + 15) & ~(uintptr_t)15);
     float *part_b = part + nch * 27 * (int64_t)cout * cin;
     // the brick kernel copies 16-channel rows as 16-byte vectors: aligned rows only
     const bool rows16 = x_cs % 8 == 0 && g_cs % 8 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(gy) % 16 == 0;
     if (g.nx % 4 == 0 && g.ny % 4 == 0 && g.nz % 4 == 0 && rows16) {
-        // bricks of 64 voxels, as many per chunk as the chunk has voxels (rounded up):
-        // at most nch chunks
-        const int64_t nb = g.nvox / 64, bricks = (chunk + 63) / 64;
-        const int64_t nbc = (nb + bricks - 1) / bricks;
-        k_conv3d_wgrad_bricks<<<dim3((unsigned)nbc, (unsigned)((cout / 16) * (cin / 16))), 64, 0, s>>>(
-            g, x, x_cs, cin, gy, g_cs, cout, bricks, part, part_b);
+        // two workgroups a compute unit, as far as the workspace's partial rows go: more only
+        // add rows to sum (96^3 x 16 -> 16 channels: 864 chunks 64 us, 494 XX)
+        const int64_t nb = (int64_t)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * (g.nz / 4);
+        const int64_t blocks = (int64_t)(cout / 16) * (cin / 16);
+        const int64_t rows = (int64_t)((ws_bytes - 256) / (((size_t)27 * cout * cin + cout) * sizeof(float)));
+        int64_t want = (512 + blocks - 1) / blocks;
+        if (want > rows) want = rows;
+        const int64_t bricks = (nb + want - 1) / want, nbc = (nb + bricks - 1) / bricks;
+        part_b = part + nbc * 27 * (int64_t)cout * cin;
+        k_conv3d_wgrad_bricks<<<dim3((unsigned)nbc, (unsigned)((cout / 16) * (cin / 16))), 256, 0, s>>>(
+            g, x, x_cs, cin, gy, g_cs, cout, (int)bricks, (int)nb, part, part_b);
         LBM_CHECK_LAUNCH();
         nch = nbc;
     } else {
@@ -908,13 +995,8 @@ extern "C" lbm_status lbm_nn_conv3d_wgrad(const int32_t n[3], const uint16_t *x,
     }
     LBM_CHECK_LAUNCH();
     }
-    const int64_t count = (int64_t)27 * cout * cin;
-    k_sum_parts<<<(unsigned)((count + 15) / 16), 256, 0, s>>>(part, nch, count, dw, accumulate);
+    sum_parts(part, nch, (int64_t)27 * cout * cin, dw, part_b, db ? cout : 0, db, accumulate, s);
     LBM_CHECK_LAUNCH();
-    if (db) {
-        k_sum_parts<<<(unsigned)((cout + 15) / 16), 256, 0, s>>>(part_b, nch, cout, db, accumulate);
-        LBM_CHECK_LAUNCH();
-    }
     return LBM_OK;
 }
 

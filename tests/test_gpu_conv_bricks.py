@@ -33,3 +33,30 @@ def test_bricks_equal_tiles(shape, cin, cout, ycs, flags):
     nn.lbm_nn_conv3d(shape, View(x), cin, w, bias, View(ya, 0, cout), cout, flags)
     nn.lbm_nn_conv3d(shape, View(xo, 4, cin), cin, w, bias, View(yb, 0, cout), cout, flags)
     assert torch.equal(ya.view(torch.int16), yb.view(torch.int16))
+
+
+@pytest.mark.parametrize("rows", [1, 40])
+@pytest.mark.parametrize("shape,cin,cout", [((8, 16, 24), 16, 16), ((12, 12, 12), 64, 32), ((4, 4, 4), 16, 48),
+                                            ((16, 28, 36), 32, 16), ((48, 48, 48), 16, 16)])
+def test_weight_gradient_bricks_equal_tiles(shape, cin, cout, rows):
+    """The same of the weight gradient: sums of at most 48^3 products of at most 6 and the
+    accumulated start stay below 2^24.  A workspace of several times the size takes more
+    chunks of bricks; 16 or more chunks take the sum with 16 threads an output."""
+    nv = shape[0] * shape[1] * shape[2]
+    gen = torch.Generator().manual_seed(nv + cout)
+    x = torch.randint(-3, 4, (nv, cin), generator=gen).to(torch.bfloat16).cuda()
+    xo = torch.zeros((nv, cin + 8), dtype=torch.bfloat16, device="cuda")
+    xo[:, 4:4 + cin] = x
+    g = torch.randint(-2, 3, (nv, cout), generator=gen).to(torch.bfloat16).cuda()
+    size = nn.lbm_nn_wgrad_workspace(shape, cin, cout)
+    out = []
+    for view, ws in ((View(x), torch.empty(rows * size + 4, dtype=torch.uint8, device="cuda")[4:]),
+                     (View(xo, 4, cin), torch.empty(size, dtype=torch.uint8, device="cuda"))):
+        dw = torch.full((27 * cin * cout,), 5.0, device="cuda")
+        db = torch.full((cout,), 5.0, device="cuda")
+        nn.lbm_nn_conv3d_wgrad(shape, view, cin, View(g), cout, dw, db, ws, True)
+        first = dw.clone()
+        nn.lbm_nn_conv3d_wgrad(shape, view, cin, View(g), cout, dw, None, ws)
+        out.append((first, dw, db))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
