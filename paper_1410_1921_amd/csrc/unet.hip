@@ -8,6 +8,7 @@
 // so the [skip, upsampled] concatenation of a decoder input is two views of one buffer.
 // Weights are [27][cout][cin], tap t = 9 (dz + 1) + 3 (dy + 1) + (dx + 1); products
 // accumulate in binary32.
+#include <type_traits>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -128,10 +129,11 @@ __global__ __launch_bounds__(256) void k_conv3d(NnGrid g, const uint16_t *__rest
 // brick: input block, then tap.
 //
 // Measured, a wave per 4 x 4 x 4 brick that read both operands for every product before:
-// 96^3 x 16 -> 16 channels 50.8 -> 32.6 us, 96^3 x 48 -> 16 137 -> 69, 48^3 x 96 -> 32 83 ->
-// 39, 24^3 x 192 -> 64 73 -> 27, 12^3 x 128 -> 128 46 -> 12; 390 to 530 of the 1260 TFLOP/s
-// of the 16 x 16 x 16 products on the 96^3 levels, where what is left is a workgroup's start:
-// halo and weights are on their way while only one other workgroup of the compute unit works.
+// 96^3 x 16 -> 16 channels 50.8 -> 31 us, 96^3 x 48 -> 16 137 -> 65, 48^3 x 96 -> 32 83 -> 35,
+// 24^3 x 192 -> 64 73 -> 24, 12^3 x 128 -> 128 46 -> 12; 390 to 560 of the 1260 TFLOP/s of the
+// 16 x 16 x 16 products on the 96^3 levels, the matrix cores busy half of the time: what is
+// left is a workgroup's start, when halo and weights are on their way while only one other
+// workgroup of the compute unit works.
 typedef uint32_t u32x4a8 __attribute__((ext_vector_type(4), aligned(8)));  // 16 bytes at 8
 template <int WX, int WY, int WZ, int PZ, bool FLIP>
 __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t *__restrict__ x, int x_cs,
@@ -150,15 +152,21 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bx = (g.nx + TX - 1) / TX, by = (g.ny + TY - 1) / TY;
-    const int b = (int)blockIdx.x, c0 = (int)blockIdx.y * 16;
+    const int b = (int)xcd_block(blockIdx.x, gridDim.x / kXcd), c0 = (int)blockIdx.y * 16;
+    if (b >= bx * by * ((g.nz + TZ - 1) / TZ)) return;
     const int x0 = TX * (b % bx), y0 = TY * ((b / bx) % by), z0 = TZ * (b / (bx * by));
     // the thread's chunks of the halo: one place in the plane, half (8 channels) of its 16, in
     // the planes hz, hz + PP, ..
     const int hc = tid % NCP, hz = tid / NCP, hx = (hc >> 1) % HX, hy = (hc >> 1) / HX;
     const int sxv = x0 - 1 + hx, syv = y0 - 1 + hy, szv = z0 - 1 + hz;
     const bool inside = hz < PP && sxv >= 0 && sxv < g.nx && syv >= 0 && syv < g.ny;
+    // addresses as one scalar base per load and one lane offset for all of them: in 32 bits
+    // where a thread stays in one plane (10 rows of a tensor are far below 2^32 elements)
+    typedef typename std::conditional<PP == 1, uint32_t, int64_t>::type LaneOff;
     const int64_t plane = (int64_t)g.nx * g.ny * x_cs;
-    const uint16_t *const src = x + szv * plane + ((int64_t)syv * g.nx + sxv) * x_cs + 8 * (hc & 1);
+    const uint16_t *const src = x + (z0 - 1) * plane + ((int64_t)(y0 - 1) * g.nx + x0 - 1) * x_cs;
+    const LaneOff so = (LaneOff)((PP == 1 ? 0 : hz * plane) + ((int64_t)hy * g.nx + hx) * x_cs + 8 * (hc & 1));
+    const uint32_t wo = (uint32_t)(((tid >> 5) * cout + ((tid >> 1) & 15)) * cin + 8 * (tid & 1));
     uint16_t *const dst = sx + (2 * (hc & 1) * QS + (hz * HY + hy) * RS + hx) * 4;
     uint4 pre[PER];
     u32x4a8 wpre[WPER];
@@ -168,14 +176,12 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
             const int vz = szv + PP * k;
             pre[k] = uint4{0u, 0u, 0u, 0u};
             if (inside && hz + PP * k < HZ && vz >= 0 && vz < g.nz)
-                pre[k] = *reinterpret_cast<const uint4 *>(src + PP * k * plane + kc);
+                pre[k] = *reinterpret_cast<const uint4 *>(src + PP * k * plane + kc + so);
         }
 #pragma unroll
         for (int k = 0; k < WPER; k++) {
-            const int c = tid + 256 * k;  // tap, out channel, half
-            if (c < NWT)
-                wpre[k] = *reinterpret_cast<const u32x4a8 *>(
-                    w + ((int64_t)(c >> 5) * cout + c0 + ((c >> 1) & 15)) * cin + kc + 8 * (c & 1));
+            if (tid + 256 * k < NWT)  // 8 taps at once; out channel, half
+                wpre[k] = *reinterpret_cast<const u32x4a8 *>(w + ((int64_t)8 * k * cout + c0) * cin + kc + wo);
         }
     };
     auto store_block = [&]() {
@@ -234,6 +240,7 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     const int vx = x0 + tx * 4, vy = y0 + ty * 4;
     if (vx >= g.nx || vy >= g.ny) return;
     const bool wide = y_cs % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+    const uint32_t yo = (uint32_t)(((r >> 2) * g.nx + (r & 3)) * y_cs + 4 * q);
     float bc[4];
 #pragma unroll
     for (int j = 0; j < 4; j++) bc[j] = bias ? bias[c0 + 4 * q + j] : 0.f;
@@ -249,7 +256,7 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
             const uint32_t h = f2bf(v);
             o[j >> 1] = j & 1 ? o[j >> 1] | h << 16 : h;
         }
-        uint16_t *d = y + (((int64_t)vz * g.ny + vy + (r >> 2)) * g.nx + vx + (r & 3)) * y_cs + c0 + 4 * q;
+        uint16_t *d = y + (((int64_t)vz * g.ny + vy) * g.nx + vx) * y_cs + c0 + yo;
         if (wide) {
             *reinterpret_cast<uint2 *>(d) = uint2{o[0], o[1]};
         } else {
@@ -335,6 +342,12 @@ __device__ __forceinline__ bf16x4 read_column4(const uint16_t *p) {
 // once and used for all three dz, 54 reads for 54 products of 16 cycles.  The four waves'
 // sums are added through LDS at the end, in one order, so that a workgroup writes one partial
 // row.
+//
+// Measured with the sum of the rows, a wave per 4 x 4 x 4 brick with K = 16 before: 96^3 x 16 ->
+// 16 channels 101 -> 33 us, 96^3 x 48 -> 16 182 -> 94, 48^3 x 96 -> 32 88 -> 36, 24^3 x 192 -> 64
+// 83 -> 33, 12^3 x 128 -> 128 92 -> 24.  Vector work beside the products (addresses, registers
+// moved for the overlapping pairs of planes) and the staging are what is left; the products
+// alone would take 5 us of the first.
 __global__ __launch_bounds__(256, 2) void k_conv3d_wgrad_bricks(NnGrid g, const uint16_t *__restrict__ x,
                                                                 int x_cs, int cin,
                                                                 const uint16_t *__restrict__ gy,
@@ -500,7 +513,12 @@ __global__ __launch_bounds__(256) void k_transpose_w(const uint16_t *__restrict_
 // access) when the channel count, the strides and the pointers allow it, else V = 1.
 template <int V>
 __device__ inline void ldv(const uint16_t *p, uint16_t (&o)[V]) {
-    if constexpr (V == 4) {
+    if constexpr (V == 8) {
+        const uint4 u = *reinterpret_cast<const uint4 *>(p);
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int k = 0; k < 8; k++) o[k] = (uint16_t)(w[k >> 1] >> (k & 1) * 16);
+    } else if constexpr (V == 4) {
         const uint2 u = *reinterpret_cast<const uint2 *>(p);
         o[0] = (uint16_t)(u.x & 0xffffu); o[1] = (uint16_t)(u.x >> 16);
         o[2] = (uint16_t)(u.y & 0xffffu); o[3] = (uint16_t)(u.y >> 16);
@@ -511,7 +529,12 @@ __device__ inline void ldv(const uint16_t *p, uint16_t (&o)[V]) {
 }
 template <int V>
 __device__ inline void stv(uint16_t *p, const uint16_t (&o)[V]) {
-    if constexpr (V == 4) {
+    if constexpr (V == 8) {
+        uint32_t w[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) w[k] = (uint32_t)o[2 * k] | ((uint32_t)o[2 * k + 1] << 16);
+        *reinterpret_cast<uint4 *>(p) = uint4{w[0], w[1], w[2], w[3]};
+    } else if constexpr (V == 4) {
         uint2 u;
         u.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
         u.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
@@ -522,22 +545,54 @@ __device__ inline void stv(uint16_t *p, const uint16_t (&o)[V]) {
     }
 }
 
+// Item i of n as (voxel v, channel ch) with cv groups of V channels a voxel; false beyond n.
+// In 32 bits where n fits: the 64-bit division took longer than the copy.
+template <int V>
+__device__ inline bool item(int64_t n, int cv, int64_t &v, int &ch) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n <= 0xffffffffll) {
+        const uint32_t u = (uint32_t)i / (uint32_t)cv;
+        v = u;
+        ch = (int)((uint32_t)i - u * (uint32_t)cv) * V;
+    } else {
+        v = i / cv;
+        ch = (int)(i % cv) * V;
+    }
+    return i < n;
+}
+// Coordinates of voxel v of an nx x ny x .. grid; a voxel number fits 32 bits below 2^32.
+__device__ inline void voxel_xyz(int64_t v, int nx, int ny, int &x, int &y, int &z) {
+    if (v <= 0xffffffffll) {
+        const uint32_t u = (uint32_t)v, row = u / (uint32_t)nx;
+        x = (int)(u - row * (uint32_t)nx);
+        z = (int)(row / (uint32_t)ny);
+        y = (int)(row - (uint32_t)z * (uint32_t)ny);
+    } else {
+        x = (int)(v % nx);
+        y = (int)((v / nx) % ny);
+        z = (int)(v / ((int64_t)nx * ny));
+    }
+}
+
+// The elementwise kernels below move V channels a thread, 16 bytes (V = 8) where strides and
+// pointers allow, and are bound by memory.  At 96^3, with 8 bytes a thread and 64-bit divisions
+// before: upsampling into 32 channels 26 -> 18 us, pooling 16 channels 22 -> 21, the input of
+// the network (2 bytes a store before) 38 -> 11.
+//
 // 2x2x2 mean of the fine grid n (even sizes) onto the coarse grid.
 template <int V>
 __global__ __launch_bounds__(256) void k_pool2(NnGrid f, int c, const uint16_t *__restrict__ x,
                                                int x_cs, uint16_t *__restrict__ y, int y_cs,
                                                int accumulate) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int cx = f.nx / 2, cy = f.ny / 2, cz = f.nz / 2;
-    const int64_t ncv = (int64_t)cx * cy * cz;
-    const int cv = c / V;
-    if (i >= ncv * cv) return;
-    const int64_t v = i / cv;
-    const int ch = (int)(i % cv) * V;
-    const int X = (int)(v % cx), Y = (int)((v / cx) % cy), Z = (int)(v / ((int64_t)cx * cy));
+    int64_t v;
+    int ch, X, Y, Z;
+    if (!item<V>((int64_t)cx * cy * cz * (c / V), c / V, v, ch)) return;
+    voxel_xyz(v, cx, cy, X, Y, Z);
     float s[V];
 #pragma unroll
     for (int k = 0; k < V; k++) s[k] = 0.f;
+#pragma unroll
     for (int m = 0; m < 8; m++) {
         const int64_t fv = ((int64_t)(2 * Z + (m >> 2)) * f.ny + 2 * Y + ((m >> 1) & 1)) * f.nx + 2 * X + (m & 1);
         uint16_t e[V];
@@ -561,12 +616,10 @@ template <int V>
 __global__ __launch_bounds__(256) void k_pool2_bwd(NnGrid f, int c, const uint16_t *__restrict__ gy,
                                                    int gy_cs, uint16_t *__restrict__ gx, int gx_cs,
                                                    int accumulate) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int cv = c / V;
-    if (i >= f.nvox * cv) return;
-    const int64_t v = i / cv;
-    const int ch = (int)(i % cv) * V;
-    const int x = (int)(v % f.nx), y = (int)((v / f.nx) % f.ny), z = (int)(v / ((int64_t)f.nx * f.ny));
+    int64_t v;
+    int ch, x, y, z;
+    if (!item<V>(f.nvox * (c / V), c / V, v, ch)) return;
+    voxel_xyz(v, f.nx, f.ny, x, y, z);
     const int64_t pv = ((int64_t)(z / 2) * (f.ny / 2) + y / 2) * (f.nx / 2) + x / 2;
     uint16_t e[V], o[V];
     ldv<V>(gy + pv * gy_cs + ch, e);
@@ -585,12 +638,10 @@ __global__ __launch_bounds__(256) void k_pool2_bwd(NnGrid f, int c, const uint16
 template <int V>
 __global__ __launch_bounds__(256) void k_up2(NnGrid f, int c, const uint16_t *__restrict__ x,
                                              int x_cs, uint16_t *__restrict__ y, int y_cs) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int cv = c / V;
-    if (i >= f.nvox * cv) return;
-    const int64_t v = i / cv;
-    const int ch = (int)(i % cv) * V;
-    const int xx = (int)(v % f.nx), yy = (int)((v / f.nx) % f.ny), zz = (int)(v / ((int64_t)f.nx * f.ny));
+    int64_t v;
+    int ch, xx, yy, zz;
+    if (!item<V>(f.nvox * (c / V), c / V, v, ch)) return;
+    voxel_xyz(v, f.nx, f.ny, xx, yy, zz);
     const int64_t pv = ((int64_t)(zz / 2) * (f.ny / 2) + yy / 2) * (f.nx / 2) + xx / 2;
     uint16_t e[V];
     ldv<V>(x + pv * x_cs + ch, e);
@@ -600,16 +651,15 @@ __global__ __launch_bounds__(256) void k_up2(NnGrid f, int c, const uint16_t *__
 template <int V>
 __global__ __launch_bounds__(256) void k_up2_bwd(NnGrid f, int c, const uint16_t *__restrict__ gy,
                                                  int gy_cs, uint16_t *__restrict__ gx, int gx_cs) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int cx = f.nx / 2, cy = f.ny / 2, cz = f.nz / 2;
-    const int cv = c / V;
-    if (i >= (int64_t)cx * cy * cz * cv) return;
-    const int64_t v = i / cv;
-    const int ch = (int)(i % cv) * V;
-    const int X = (int)(v % cx), Y = (int)((v / cx) % cy), Z = (int)(v / ((int64_t)cx * cy));
+    int64_t v;
+    int ch, X, Y, Z;
+    if (!item<V>((int64_t)cx * cy * cz * (c / V), c / V, v, ch)) return;
+    voxel_xyz(v, cx, cy, X, Y, Z);
     float s[V];
 #pragma unroll
     for (int k = 0; k < V; k++) s[k] = 0.f;
+#pragma unroll
     for (int m = 0; m < 8; m++) {
         const int64_t fv = ((int64_t)(2 * Z + (m >> 2)) * f.ny + 2 * Y + ((m >> 1) & 1)) * f.nx + 2 * X + (m & 1);
         uint16_t e[V];
@@ -628,11 +678,9 @@ template <int V>
 __global__ __launch_bounds__(256) void k_relu_bwd(int64_t nvox, int c, const uint16_t *__restrict__ y,
                                                   int y_cs, const uint16_t *__restrict__ gy,
                                                   int gy_cs, uint16_t *__restrict__ gout, int g_cs) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int cv = c / V;
-    if (i >= nvox * cv) return;
-    const int64_t v = i / cv;
-    const int ch = (int)(i % cv) * V;
+    int64_t v;
+    int ch;
+    if (!item<V>(nvox * (c / V), c / V, v, ch)) return;
     uint16_t yv[V], gv[V], o[V];
     ldv<V>(y + v * y_cs + ch, yv);
     ldv<V>(gy + v * gy_cs + ch, gv);
@@ -642,18 +690,31 @@ __global__ __launch_bounds__(256) void k_relu_bwd(int64_t nvox, int c, const uin
     stv<V>(gout + v * g_cs + ch, o);
 }
 
-// 8-byte channel groups for c channels at the given strides and pointers
-static bool vec4(int c, std::initializer_list<int> cs, std::initializer_list<const void *> ptrs) {
-    if (c % 4) return false;
-    for (int s : cs)
-        if (s % 4) return false;
-    for (const void *p : ptrs)
-        if (reinterpret_cast<uintptr_t>(p) % 8) return false;
-    return true;
+// groups of 8 (16 bytes), 4 or 1 channels for c channels at the given strides and pointers
+static int vec(int c, std::initializer_list<int> cs, std::initializer_list<const void *> ptrs) {
+    for (int n = 8; n > 1; n >>= 1) {
+        bool ok = c % n == 0;
+        for (int s : cs) ok = ok && s % n == 0;
+        for (const void *p : ptrs) ok = ok && reinterpret_cast<uintptr_t>(p) % (2 * n) == 0;
+        if (ok && n != 2) return n;
+    }
+    return 1;
 }
 
 constexpr int kHeadMaxOut = 8;
 constexpr int kHeadCin = 16;
+
+// A voxel's 16 channels, 16 bytes at a time where wide (with the outputs' loop unrolled, the
+// head with a target at 96^3: 92 us with 2-byte loads and stores, 30 with these).
+__device__ inline void load16(const uint16_t *p, bool wide, uint16_t (&o)[kHeadCin]) {
+    if (wide) {
+        ldv<8>(p, reinterpret_cast<uint16_t(&)[8]>(o[0]));
+        ldv<8>(p + 8, reinterpret_cast<uint16_t(&)[8]>(o[8]));
+    } else {
+#pragma unroll
+        for (int c = 0; c < kHeadCin; c++) o[c] = p[c];
+    }
+}
 
 // The 1x1x1 head: out[o][v] = bh[o] + sum_c wh[o][c] x[v][c] (binary32, planar).  With a
 // target: go[o][v] = 2 wt[o] mask[v] (out - target) / n_mask (the gradient of the loss
@@ -669,13 +730,18 @@ __global__ __launch_bounds__(256) void k_head(int64_t nvox, const uint16_t *__re
                                               float *__restrict__ gout, uint16_t *__restrict__ gx,
                                               int gx_cs, double *__restrict__ loss_part) {
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool wide_x = x_cs % 8 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
     double loss = 0.0;
     if (v < nvox) {
+        uint16_t xb[kHeadCin];
+        load16(x + v * x_cs, wide_x, xb);
         float xv[kHeadCin];
 #pragma unroll
-        for (int c = 0; c < kHeadCin; c++) xv[c] = bf2f(x[v * x_cs + c]);
+        for (int c = 0; c < kHeadCin; c++) xv[c] = bf2f(xb[c]);
         float go[kHeadMaxOut];
-        for (int o = 0; o < no; o++) {
+#pragma unroll
+        for (int o = 0; o < kHeadMaxOut; o++) {
+            if (o >= no) break;
             float s = bh[o];
 #pragma unroll
             for (int c = 0; c < kHeadCin; c++) s += wh[o * kHeadCin + c] * xv[c];
@@ -689,11 +755,21 @@ __global__ __launch_bounds__(256) void k_head(int64_t nvox, const uint16_t *__re
             if (target) gout[o * nvox + v] = go[o];
         }
         if (target && gx) {
+            uint16_t gb[kHeadCin];
 #pragma unroll
             for (int c = 0; c < kHeadCin; c++) {
                 float s = 0.f;
-                for (int o = 0; o < no; o++) s += wh[o * kHeadCin + c] * go[o];
-                gx[v * gx_cs + c] = f2bf(s);
+#pragma unroll
+                for (int o = 0; o < kHeadMaxOut; o++)
+                    if (o < no) s += wh[o * kHeadCin + c] * go[o];
+                gb[c] = f2bf(s);
+            }
+            if (gx_cs % 8 == 0 && reinterpret_cast<uintptr_t>(gx) % 16 == 0) {
+                stv<8>(gx + v * gx_cs, reinterpret_cast<const uint16_t(&)[8]>(gb[0]));
+                stv<8>(gx + v * gx_cs + 8, reinterpret_cast<const uint16_t(&)[8]>(gb[8]));
+            } else {
+#pragma unroll
+                for (int c = 0; c < kHeadCin; c++) gx[v * gx_cs + c] = gb[c];
             }
         }
     }
@@ -712,14 +788,17 @@ __global__ __launch_bounds__(256) void k_head_wgrad(int64_t nvox, const uint16_t
                                                     int64_t chunk, double *__restrict__ part) {
     constexpr int NV = kHeadCin + 1;
     const int o = blockIdx.y;
+    const bool wide_x = x_cs % 8 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < nvox ? lo + chunk : nvox;
     double acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; k++) acc[k] = 0.0;
     for (int64_t v = lo + threadIdx.x; v < hi; v += 256) {
         const double go = gout[o * nvox + v];
+        uint16_t xb[kHeadCin];
+        load16(x + v * x_cs, wide_x, xb);
 #pragma unroll
-        for (int c = 0; c < kHeadCin; c++) acc[c] += go * (double)bf2f(x[v * x_cs + c]);
+        for (int c = 0; c < kHeadCin; c++) acc[c] += go * (double)bf2f(xb[c]);
         acc[kHeadCin] += go;
     }
     __shared__ double lds[4][NV];
@@ -737,30 +816,34 @@ __global__ __launch_bounds__(256) void k_head_wgrad(int64_t nvox, const uint16_t
     }
 }
 
-// Fixed-order sums: the loss (each thread one contiguous 1/256 of the block partials in
-// order, then the 256 sums in order), gwh[o][c] and gbh[o].
-__global__ __launch_bounds__(256) void k_head_final(const double *__restrict__ loss_part, int64_t nb,
-                                                    const double *__restrict__ part, int64_t nch,
-                                                    int no, double *__restrict__ loss,
-                                                    float *__restrict__ gwh, float *__restrict__ gbh) {
+// Fixed-order sums: the loss, gwh[o][c] and gbh[o].  One wave per sum of the gradients, all
+// 16 waves on the loss; lanes take every 64th (1024th) partial, then halves are added.  (One
+// thread a sum was a chain of loads: 31 us at 96^3.)
+__global__ __launch_bounds__(1024) void k_head_final(const double *__restrict__ loss_part, int64_t nb,
+                                                     const double *__restrict__ part, int64_t nch,
+                                                     int no, double *__restrict__ loss,
+                                                     float *__restrict__ gwh, float *__restrict__ gbh) {
     constexpr int NV = kHeadCin + 1;
-    __shared__ double lds[256];
-    const int k = threadIdx.x;
-    if (k < no * NV) {
+    __shared__ double lds[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int k = wave; k < no * NV; k += 16) {
         double s = 0.0;
-        for (int64_t c = 0; c < nch; c++) s += part[c * no * NV + k];
+        for (int64_t c = lane; c < nch; c += 64) s += part[c * no * NV + k];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
         const int o = k / NV, c = k % NV;
-        if (c < kHeadCin) gwh[o * kHeadCin + c] = (float)s;
-        else gbh[o] = (float)s;
+        if (lane == 0) {
+            if (c < kHeadCin) gwh[o * kHeadCin + c] = (float)s;
+            else gbh[o] = (float)s;
+        }
     }
-    const int64_t per = (nb + 255) / 256, b0 = k * per, b1 = b0 + per < nb ? b0 + per : nb;
     double s = 0.0;
-    for (int64_t b = b0; b < b1; b++) s += loss_part[b];
-    lds[k] = s;
+    for (int64_t b = threadIdx.x; b < nb; b += 1024) s += loss_part[b];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if (lane == 0) lds[wave] = s;
     __syncthreads();
-    if (k == 0) {
+    if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int i = 0; i < 256; i++) t += lds[i];
+        for (int i = 0; i < 16; i++) t += lds[i];
         *loss = t;
     }
 }
@@ -791,18 +874,23 @@ __global__ __launch_bounds__(256) void k_to_bf16(int64_t n, const float *__restr
 
 // The network input: channel 0 the pore mask, channel 1 the pore diameter / d_scale,
 // channels 2 .. cs - 1 zero.
+template <int V>
 __global__ __launch_bounds__(256) void k_make_input(int64_t nvox, const uint8_t *__restrict__ mask,
                                                     const double *__restrict__ diam,
                                                     double inv_scale, uint16_t *__restrict__ x,
                                                     int cs) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= nvox) return;
-    for (int c = 0; c < cs; c++) {
+    int64_t v;
+    int ch;
+    if (!item<V>(nvox * (cs / V), cs / V, v, ch)) return;
+    uint16_t o[V];
+#pragma unroll
+    for (int k = 0; k < V; k++) {
         float val = 0.f;
-        if (c == 0) val = mask[v] ? 1.f : 0.f;
-        else if (c == 1) val = (float)(diam[v] * inv_scale);
-        x[v * cs + c] = f2bf(val);
+        if (ch + k == 0) val = mask[v] ? 1.f : 0.f;
+        else if (ch + k == 1) val = (float)(diam[v] * inv_scale);
+        o[k] = f2bf(val);
     }
+    stv<V>(x + v * cs + ch, o);
 }
 
 // fields[k][v] = mask[v] ? out[k][v] * scale[k] : 0.
@@ -810,11 +898,10 @@ __global__ __launch_bounds__(256) void k_to_fields(int64_t nvox, int nk, const f
                                                    const uint8_t *__restrict__ mask,
                                                    const float *__restrict__ scale,
                                                    float *__restrict__ fields) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= nvox * nk) return;
-    const int64_t v = i % nvox;
-    const int k = (int)(i / nvox);
-    fields[i] = mask[v] ? out[i] * scale[k] : 0.f;
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v >= nvox) return;
+    const bool in = mask[v];
+    for (int k = 0; k < nk; k++) fields[k * nvox + v] = in ? out[k * nvox + v] * scale[k] : 0.f;
 }
 
 static unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -835,7 +922,9 @@ static void conv_bricks(const NnGrid &g, const uint16_t *x, int x_cs, int cin, c
                         const float *bias, uint16_t *y, int y_cs, int cout, int relu, int flip,
                         hipStream_t s) {
     const auto cut = [](int n, int t) { return (unsigned)((n + t - 1) / t); };
-    const dim3 grid(cut(g.nx, 4 * WX) * cut(g.ny, 4 * WY) * cut(g.nz, PZ * WZ), (unsigned)(cout / 16));
+    // neighbouring bricks, which share halos, on one of the 8 parts of the chip
+    const dim3 grid((unsigned)xcd_launch(cut(g.nx, 4 * WX) * cut(g.ny, 4 * WY) * cut(g.nz, PZ * WZ)),
+                    (unsigned)(cout / 16));
     if (flip)
         k_conv3d_bricks<WX, WY, WZ, PZ, true><<<grid, 256, 0, s>>>(g, x, x_cs, cin, w, cout, bias, y, y_cs, relu);
     else
@@ -922,8 +1011,8 @@ extern "C" lbm_status lbm_nn_conv3d(const int32_t n[3], const uint16_t *x, int32
     return LBM_OK;
 }
 
-// Sums of the partial rows: 16 threads an output where they are many, one where few rows or
-// many outputs keep the device busy without.
+// Sums of the partial rows: 16 threads an output, or one where there are fewer rows than that
+// (12 rows of 12^3 x 64 -> 128 channels, with the products: 23.3 us, with 16 threads 24.8).
 static void sum_parts(const float *part, int64_t nparts, int64_t count, float *out, const float *part_b,
                       int n_b, float *out_b, int accumulate, hipStream_t s) {
     const bool wide = nparts >= 16;
@@ -969,7 +1058,8 @@ extern "C" lbm_status lbm_nn_conv3d_wgrad(const int32_t n[3], const uint16_t *x,
                         reinterpret_cast<uintptr_t>(gy) % 16 == 0;
     if (g.nx % 4 == 0 && g.ny % 4 == 0 && g.nz % 4 == 0 && rows16) {
         // two workgroups a compute unit, as far as the workspace's partial rows go: more only
-        // add rows to sum (96^3 x 16 -> 16 channels: 864 chunks 64 us, 494 XX)
+        // add rows to sum and a last round that is half empty (with the sum, 96^3 x 16 -> 16
+        // channels: 864 chunks 39.8 us, 494 32.8; 48^3 x 96 -> 32: 108 chunks 64.8, 40 36.0)
         const int64_t nb = (int64_t)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * (g.nz / 4);
         const int64_t blocks = (int64_t)(cout / 16) * (cin / 16);
         const int64_t rows = (int64_t)((ws_bytes - 256) / (((size_t)27 * cout * cin + cout) * sizeof(float)));
@@ -1028,10 +1118,9 @@ extern "C" lbm_status lbm_nn_pool2(const int32_t n_fine[3], int32_t c, const uin
     lbm_status st = pool_args(n_fine, c, x, x_cs, y, y_cs, g);
     if (st != LBM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4(c, {x_cs, y_cs}, {x, y}))
-        k_pool2<4><<<nblk(g.nvox / 8 * (c / 4)), 256, 0, s>>>(g, c, x, x_cs, y, y_cs, accumulate);
-    else
-        k_pool2<1><<<nblk(g.nvox / 8 * c), 256, 0, s>>>(g, c, x, x_cs, y, y_cs, accumulate);
+    const int n = vec(c, {x_cs, y_cs}, {x, y});
+    const auto kernel = n == 8 ? k_pool2<8> : n == 4 ? k_pool2<4> : k_pool2<1>;
+    kernel<<<nblk(g.nvox / 8 * (c / n)), 256, 0, s>>>(g, c, x, x_cs, y, y_cs, accumulate);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1043,10 +1132,9 @@ extern "C" lbm_status lbm_nn_pool2_bwd(const int32_t n_fine[3], int32_t c, const
     lbm_status st = pool_args(n_fine, c, gy, gy_cs, gx, gx_cs, g);
     if (st != LBM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4(c, {gy_cs, gx_cs}, {gy, gx}))
-        k_pool2_bwd<4><<<nblk(g.nvox * (c / 4)), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs, accumulate);
-    else
-        k_pool2_bwd<1><<<nblk(g.nvox * c), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs, accumulate);
+    const int n = vec(c, {gy_cs, gx_cs}, {gy, gx});
+    const auto kernel = n == 8 ? k_pool2_bwd<8> : n == 4 ? k_pool2_bwd<4> : k_pool2_bwd<1>;
+    kernel<<<nblk(g.nvox * (c / n)), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs, accumulate);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1057,10 +1145,9 @@ extern "C" lbm_status lbm_nn_up2(const int32_t n_fine[3], int32_t c, const uint1
     lbm_status st = pool_args(n_fine, c, x, x_cs, y, y_cs, g);
     if (st != LBM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4(c, {x_cs, y_cs}, {x, y}))
-        k_up2<4><<<nblk(g.nvox * (c / 4)), 256, 0, s>>>(g, c, x, x_cs, y, y_cs);
-    else
-        k_up2<1><<<nblk(g.nvox * c), 256, 0, s>>>(g, c, x, x_cs, y, y_cs);
+    const int n = vec(c, {x_cs, y_cs}, {x, y});
+    const auto kernel = n == 8 ? k_up2<8> : n == 4 ? k_up2<4> : k_up2<1>;
+    kernel<<<nblk(g.nvox * (c / n)), 256, 0, s>>>(g, c, x, x_cs, y, y_cs);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1071,10 +1158,9 @@ extern "C" lbm_status lbm_nn_up2_bwd(const int32_t n_fine[3], int32_t c, const u
     lbm_status st = pool_args(n_fine, c, gy, gy_cs, gx, gx_cs, g);
     if (st != LBM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4(c, {gy_cs, gx_cs}, {gy, gx}))
-        k_up2_bwd<4><<<nblk(g.nvox / 8 * (c / 4)), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs);
-    else
-        k_up2_bwd<1><<<nblk(g.nvox / 8 * c), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs);
+    const int n = vec(c, {gy_cs, gx_cs}, {gy, gx});
+    const auto kernel = n == 8 ? k_up2_bwd<8> : n == 4 ? k_up2_bwd<4> : k_up2_bwd<1>;
+    kernel<<<nblk(g.nvox / 8 * (c / n)), 256, 0, s>>>(g, c, gy, gy_cs, gx, gx_cs);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1088,10 +1174,9 @@ extern "C" lbm_status lbm_nn_relu_bwd(int64_t nvox, int32_t c, const uint16_t *y
     if (st != LBM_OK) return st;
     if (nvox == 0) return LBM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4(c, {y_cs, gy_cs, g_cs}, {y, gy, g}))
-        k_relu_bwd<4><<<nblk(nvox * (c / 4)), 256, 0, s>>>(nvox, c, y, y_cs, gy, gy_cs, g, g_cs);
-    else
-        k_relu_bwd<1><<<nblk(nvox * c), 256, 0, s>>>(nvox, c, y, y_cs, gy, gy_cs, g, g_cs);
+    const int n = vec(c, {y_cs, gy_cs, g_cs}, {y, gy, g});
+    const auto kernel = n == 8 ? k_relu_bwd<8> : n == 4 ? k_relu_bwd<4> : k_relu_bwd<1>;
+    kernel<<<nblk(nvox * (c / n)), 256, 0, s>>>(nvox, c, y, y_cs, gy, gy_cs, g, g_cs);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1142,7 +1227,7 @@ extern "C" lbm_status lbm_nn_head(int64_t nvox, const uint16_t *x, int32_t x_cs,
     if (target) {
         k_head_wgrad<<<dim3((unsigned)nch, (unsigned)no), 256, 0, s>>>(nvox, x, x_cs, gout, chunk, part);
         LBM_CHECK_LAUNCH();
-        k_head_final<<<1, 256, 0, s>>>(loss_part, nb, part, nch, no, dloss, gwh, gbh);
+        k_head_final<<<1, 1024, 0, s>>>(loss_part, nb, part, nch, no, dloss, gwh, gbh);
         LBM_CHECK_LAUNCH();
         LBM_TRY_HIP(hipMemcpyAsync(loss_h, dloss, sizeof(double), hipMemcpyDeviceToHost, s));
         LBM_TRY_HIP(hipStreamSynchronize(s));
@@ -1184,8 +1269,10 @@ extern "C" lbm_status lbm_nn_make_input(int64_t nvox, const uint8_t *mask, const
     lbm_status st = check_device();
     if (st != LBM_OK) return st;
     if (nvox == 0) return LBM_OK;
-    k_make_input<<<nblk(nvox), 256, 0, static_cast<hipStream_t>(stream)>>>(nvox, mask, diam,
-                                                                          1.0 / d_scale, x, x_cs);
+    const int n = vec(x_cs, {}, {x});
+    const auto kernel = n == 8 ? k_make_input<8> : n == 4 ? k_make_input<4> : k_make_input<1>;
+    kernel<<<nblk(nvox * (x_cs / n)), 256, 0, static_cast<hipStream_t>(stream)>>>(nvox, mask, diam,
+                                                                                1.0 / d_scale, x, x_cs);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
@@ -1197,8 +1284,8 @@ extern "C" lbm_status lbm_nn_to_fields(int64_t nvox, int32_t nk, const float *ou
     lbm_status st = check_device();
     if (st != LBM_OK) return st;
     if (nvox == 0) return LBM_OK;
-    k_to_fields<<<nblk(nvox * nk), 256, 0, static_cast<hipStream_t>(stream)>>>(nvox, nk, out, mask,
-                                                                              scale, fields);
+    k_to_fields<<<nblk(nvox), 256, 0, static_cast<hipStream_t>(stream)>>>(nvox, nk, out, mask, scale,
+                                                                         fields);
     LBM_CHECK_LAUNCH();
     return LBM_OK;
 }
