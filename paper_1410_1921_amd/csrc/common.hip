@@ -153,15 +153,15 @@ __device__ inline bool column_row(const Grid &g, int64_t r, int &y, int &z) {
     return y < g.ny && z < g.nz;
 }
 
-// Exclusive scan, in list order, of the segment counts held in rank[].base, in place,
-// offset by id_base (the id of the lattice's first node); the count goes to *total.
-// One block of 1024 threads, each over a run of rows.
-__global__ __launch_bounds__(1024) void k_seg_scan(RankWord *__restrict__ rank, Grid g,
-                                                   int32_t *__restrict__ total, uint32_t id_base) {
-    __shared__ int64_t part[1024];
-    const int64_t nrows = (int64_t)g.ncz * g.ncy * kCol * kCol;
-    const int64_t per = (nrows + 1023) / 1024;
-    const int64_t lo = threadIdx.x * per, hi = lo + per < nrows ? lo + per : nrows;
+// Exclusive scan, in list order, of the segment counts held in rank[].base, in place, offset
+// by id_base (the id of the lattice's first node); the count goes to *total.  A block owns
+// 256 runs of per rows, at most kScanBlocks blocks the lattice.  The first kernel leaves block
+// k's sum in rank[k].base_hi, which holds nothing until k_seg_fill, and there are fewer blocks
+// than segments; the second adds the sums before its own, scans its threads' and numbers its
+// segments.  Bound by memory and latency (one block of 1024 threads for the whole lattice
+// before: 512^3 4.05 ms, 128^3 72 us; now 55 and 8 us for the two).
+constexpr int kScanBlocks = 1024;
+__device__ inline int64_t run_count(const RankWord *__restrict__ rank, const Grid &g, int64_t lo, int64_t hi) {
     int64_t sum = 0;
     int y, z;
     for (int64_t r = lo; r < hi; r++) {
@@ -169,19 +169,45 @@ __global__ __launch_bounds__(1024) void k_seg_scan(RankWord *__restrict__ rank, 
         const int64_t s0 = g.seg(0, y, z);
         for (int sx = 0; sx < g.nseg; sx++) sum += rank[s0 + sx].base;
     }
-    part[threadIdx.x] = sum;
+    return sum;
+}
+// Sum of v over the block's 256 threads (in every thread) and over those before its own.
+__device__ inline int64_t block_sum(int64_t v, int64_t &before) {
+    __shared__ int64_t waves[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t inc = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    if (lane == 63) waves[wave] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int i = 0; i < 1024; i++) {
-            const int64_t v = part[i];
-            part[i] = run;
-            run += v;
-        }
-        *total = (int32_t)run;
+    int64_t all = 0;
+    before = inc - v;
+    for (int w = 0; w < 4; w++) {
+        if (w < wave) before += waves[w];
+        all += waves[w];
     }
     __syncthreads();
-    int64_t run = part[threadIdx.x] + id_base;
+    return all;
+}
+__global__ __launch_bounds__(256) void k_seg_sums(RankWord *__restrict__ rank, Grid g, int64_t nrows, int64_t per) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, lo = t * per;
+    int64_t before;
+    const int64_t all = block_sum(run_count(rank, g, lo, lo + per < nrows ? lo + per : nrows), before);
+    if (threadIdx.x == 0) rank[blockIdx.x].base_hi = (uint32_t)all;
+}
+__global__ __launch_bounds__(256) void k_seg_scan(RankWord *__restrict__ rank, Grid g, int64_t nrows, int64_t per,
+                                                  int32_t *__restrict__ total, uint32_t id_base) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, lo = t * per;
+    const int64_t hi = lo + per < nrows ? lo + per : nrows;
+    int64_t earlier = 0, before, unused;
+    for (uint32_t k = threadIdx.x; k < blockIdx.x; k += 256) earlier += rank[k].base_hi;
+    earlier = block_sum(earlier, unused);
+    const int64_t all = block_sum(run_count(rank, g, lo, hi), before);
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = (int32_t)(earlier + all);
+    int64_t run = earlier + before + id_base;
+    int y, z;
     for (int64_t r = lo; r < hi; r++) {
         if (!column_row(g, r, y, z)) continue;
         const int64_t s0 = g.seg(0, y, z);
@@ -216,7 +242,12 @@ lbm_status layout_count(const Grid &g, const uint8_t *fluid, RankWord *rank, int
     const int64_t blocks = (g.nsegs() + 3) / 4;
     k_seg_count<<<(unsigned)blocks, 256, 0, s>>>(g, fluid, rank);
     LBM_CHECK_LAUNCH();
-    k_seg_scan<<<1, 1024, 0, s>>>(rank, g, total_d, id_base);
+    const int64_t nrows = (int64_t)g.ncz * g.ncy * kCol * kCol;
+    const int64_t per = (nrows + 256 * kScanBlocks - 1) / (256 * kScanBlocks);
+    const unsigned nscan = (unsigned)((nrows + 256 * per - 1) / (256 * per));
+    k_seg_sums<<<nscan, 256, 0, s>>>(rank, g, nrows, per);
+    LBM_CHECK_LAUNCH();
+    k_seg_scan<<<nscan, 256, 0, s>>>(rank, g, nrows, per, total_d, id_base);
     LBM_CHECK_LAUNCH();
     int32_t total = 0;
     LBM_TRY_HIP(hipMemcpyAsync(&total, total_d, sizeof(int32_t), hipMemcpyDeviceToHost, s));

@@ -37,3 +37,19 @@ def test_row_ends(orc, nx, pressure):
     if pressure is None:
         _, _, us, _ = lbm.lbm_flow_solve_batch([g, g], want_u=True, group_bytes=-1, **kw)
         assert torch.equal(us[1], r.field)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 5), (16, 33, 70), (530, 530, 3)])
+def test_numbering(orc, shape):
+    """The scan that numbers the nodes: one block, some, and more rows (34 x 34 columns of 256)
+    than the largest grid has threads, so that a thread takes two."""
+    m = W.random_mask(shape, 0.6, 5) if shape[0] > 1 else np.ones(shape, np.uint8)
+    kw = dict(tau=0.8, force=(1e-5, 2e-6, -3e-6), fixed_steps=4, check_every=2)
+    o = orc.flow_solve(m, **kw)
+    nodes = np.flatnonzero(m.reshape(-1))
+    vox = nodes[np.random.default_rng(1).integers(0, len(nodes), 20000)]
+    fo = o["f"].reshape(-1, 19)[vox] - W19
+    r = lbm.lbm_flow_solve(torch.from_numpy(m).cuda(), storage=lbm.LBM_STORE_FP64, **kw)
+    f, flag = lbm.lbm_flow_sample(r.workspace, vox)
+    assert flag.all()
+    assert np.abs(f - fo).max() <= 1e-12
