@@ -436,14 +436,6 @@ __device__ inline void ghost_node(const R (&f)[19], R ref, R Fx, R Fy, R Fz, R d
     }
 }
 
-// A 32-bit offset as a value of the current block, where its extension to 64 bits then is
-// part of the access (carried over from another block it costs a 64-bit addition each).
-__device__ inline uint32_t here(uint32_t o) {
-    asm("" : "+v"(o));
-    return o;
-}
-__device__ inline int64_t here(int64_t o) { return o; }
-
 // The node a population is pulled from: its id (meaningless unless fluid) and the
 // reference density there.
 struct Pull {
@@ -451,32 +443,6 @@ struct Pull {
     float r;
     bool fluid;
 };
-
-// Byte offset of population 0 of node m, raised by 3 arrays of 256 so that the offset of
-// a neighbouring array (a bounced population is read from the opposite direction's) is
-// never negative; the array's own offset goes into the uniform base pointer.
-template <class T, class Off>
-__device__ inline Off pop_offset(int m) {
-    if constexpr (std::is_same<Off, uint32_t>::value)
-        return __umul24((uint32_t)m >> 8, 18u * 256u * (uint32_t)sizeof(T)) +
-               ((uint32_t)m * (uint32_t)sizeof(T) + 768u * (uint32_t)sizeof(T));
-    else
-        return (Off)((uint32_t)m >> 8) * (18 * 256 * (int64_t)sizeof(T)) +
-               ((int64_t)m * (int64_t)sizeof(T) + 768 * (int64_t)sizeof(T));
-}
-
-// An array's base address in scalar registers of its own, so that an access adds only its
-// 32-bit offset (the compiler would fold the array's constant into a 64-bit vector
-// addition per access).  Global address space: the base keeps it through the barrier.
-typedef __attribute__((address_space(1))) char gchar;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-template <class T>
-using gptr = __attribute__((address_space(1))) T *;
-__device__ inline gchar *array_base(const void *p) {
-    gchar *q = (gchar *)p;
-    asm("" : "+s"(q));
-    return q;
-}
 
 // The update of fluid node n at (x, y, z) whose 18 pull sources are resolved: src[i] is
 // the node at x - e_i, not fluid when that voxel is solid (half-way bounce-back); `ghost`

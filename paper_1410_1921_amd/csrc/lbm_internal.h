@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of liblbm.so.
 #pragma once
 
+#include <type_traits>
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -297,16 +298,53 @@ std::vector<BatchGroup> form_groups(const std::vector<int32_t> &act,
 lbm_status reduce_partials(const double *partials, int64_t nblocks, int nv, double *res,
                            hipStream_t s);
 
+// ---------------------------------------------------------------- D3Q19 populations
+// Population i of fluid node m: blocks of 256 nodes, each with its 19 arrays of 256 side by
+// side.
+//
+// Byte offset of population 0 of node m, raised by 3 arrays of 256 so that the offset of
+// a neighbouring array (a bounced population is read from the opposite direction's) is
+// never negative; the array's own offset goes into the uniform base pointer.
+template <class T, class Off>
+__device__ inline Off pop_offset(int m) {
+    if constexpr (std::is_same<Off, uint32_t>::value)
+        return __umul24((uint32_t)m >> 8, 18u * 256u * (uint32_t)sizeof(T)) +
+               ((uint32_t)m * (uint32_t)sizeof(T) + 768u * (uint32_t)sizeof(T));
+    else
+        return (Off)((uint32_t)m >> 8) * (18 * 256 * (int64_t)sizeof(T)) +
+               ((int64_t)m * (int64_t)sizeof(T) + 768 * (int64_t)sizeof(T));
+}
+
+// An array's base address in scalar registers of its own, so that an access adds only its
+// 32-bit offset (the compiler would fold the array's constant into a 64-bit vector
+// addition per access).  Global address space: the base keeps it through the barrier.
+typedef __attribute__((address_space(1))) char gchar;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <class T>
+using gptr = __attribute__((address_space(1))) T *;
+__device__ inline gchar *array_base(const void *p) {
+    gchar *q = (gchar *)p;
+    asm("" : "+s"(q));
+    return q;
+}
+
+// A 32-bit offset as a value of the current block, where its extension to 64 bits then is
+// part of the access (carried over from another block it costs a 64-bit addition each).
+__device__ inline uint32_t here(uint32_t o) {
+    asm("" : "+v"(o));
+    return o;
+}
+__device__ inline int64_t here(int64_t o) { return o; }
+
 // ---------------------------------------------------------------- sparse layout
 // Node ids are found through the rank map: one 16-byte word per row segment, holding
 // the segment's 64-bit occupancy (bit x % 64) and the id of its first fluid node, so a
 // voxel's id is base + popcount(bits below it).  At 1/4 byte per voxel the map stays
 // cache resident.
-// Each 32-bit half of the occupancy is stored beside the id of its own first fluid node,
-// so that a lookup may load the 8 bytes of one half.  The flow sweep does (18 lookups in
-// flight per node: half the registers lets its moment-space collision run 6 waves per
-// SIMD instead of 4, 4.5 % faster at 512^3); the mass-transport sweeps load whole words,
-// which measured faster for them (D3Q7 at 128^3: 10.2 against 10.8 us per step).
+// Each 32-bit half of the occupancy is stored beside the id of its own first fluid node, so
+// that a lookup may load the 8 bytes of one half, and one half of a row answers for x - 1, x
+// and x + 1: the D3Q19 sweeps read nine halves for their 18 neighbours.  The D3Q7 sweep loads
+// whole words, which measured faster for it (128^3: 10.2 against 10.8 us per step).
 struct alignas(16) RankWord {
     uint32_t lo, base;     // occupancy bits 0-31; id of the segment's first fluid node
     uint32_t hi, base_hi;  // occupancy bits 32-63; id of the first fluid node among them

@@ -53,3 +53,23 @@ def test_numbering(orc, shape):
     f, flag = lbm.lbm_flow_sample(r.workspace, vox)
     assert flag.all()
     assert np.abs(f - fo).max() <= 1e-12
+
+
+@pytest.mark.parametrize("nx", [2, 31, 32, 33, 63, 64, 65, 96, 97, 130])
+def test_row_ends_diffusion(orc, nx):
+    """The D3Q19 mass-transport sweep at the same row ends; the bar on the populations is the
+    one of the ragged parity cases (binary32 deviations of a field of order 1)."""
+    m = W.random_mask((4, 7, nx), 0.8, nx)
+    diam = W.hash_field(m.shape, nx, 1.0, 40.0).astype(np.float64) * m
+    tg = np.where(m == 1, orc.tau_g(diam, 20.0, 1.0), 1.0)
+    kw = dict(d_ref_nm=30.0, voxel_nm=1.5, c_in=0.8, c_out=0.3, fixed_steps=100, check_every=50,
+              want_c=True, lattice=lbm.LBM_LATTICE_D3Q19)
+    g, d = torch.from_numpy(m).cuda(), torch.from_numpy(diam).cuda()
+    r = lbm.lbm_knudsen_solve(g, d, **kw)
+    o = orc.diffusion19_solve(m, tg, 0.8, 0.3, fixed_steps=100, check_every=50)
+    vox = np.flatnonzero(m.reshape(-1))
+    gs, _, flag = lbm.lbm_knudsen_sample(r.workspace, vox)
+    assert flag.all()
+    assert np.abs(gs - o["g"].reshape(-1, 19)[vox]).max() < 2e-6
+    w = lbm.lbm_knudsen_solve(g, d, variant=lbm.LBM_VARIANT_OFF64, **kw)
+    assert torch.equal(w.field, r.field)
