@@ -1207,8 +1207,12 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
                          : r.npt == 4 ? reinterpret_cast<const void *>(&k_resident7<4>)
                                       : reinterpret_cast<const void *>(&k_resident7<5>);
     void *args[] = {&a};
-    LBM_TRY_HIP(hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
-                                           dim3((unsigned)(r.threads + kResSenders)), args, 0, s));
+    // refused (fewer compute units than the device names, say): plain sweeps do the steps
+    if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
+                                   dim3((unsigned)(r.threads + kResSenders)), args, 0, s) != hipSuccess) {
+        (void)hipGetLastError();
+        r.on = false;
+    }
     return LBM_OK;
 }
 
@@ -1235,10 +1239,12 @@ static lbm_status kn_launch(const KnWs &w, const Grid &g, int64_t nf, KnHeader &
         if (res && res->on && !pending && plain >= kResMinSteps) {
             const lbm_status st = resident_steps(w, g, nf, w.steady[h.frame], cur, plain, *res, s);
             if (st != LBM_OK) return st;
-            a.skip = w.abort;
-            cur ^= 1;
-            t += plain - 1;
-            continue;
+            if (res->on) {
+                a.skip = w.abort;
+                cur ^= 1;
+                t += plain - 1;
+                continue;
+            }
         }
         if (pending) {
             a.shift = w.trans;
