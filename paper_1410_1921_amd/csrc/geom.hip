@@ -34,7 +34,7 @@ constexpr int kRows = 4;
 // stands for it), and two touching runs are joined once, at their first contact, found
 // from the bits of the two rows.  One union per voxel and neighbour, straight in global
 // memory, took 2.9 ms at 128^3 (porosity 0.40) and 46 ms at 512^3 (with one atomic per
-// wave on each of three counters in the last pass, 33 ms of it); now 0.16 and 2.6 ms.
+// wave on each of three counters in the last pass, 33 ms of it); now 0.13 and 2.5 ms.
 constexpr int kTy = 8, kTz = 8;  // rows of a labelling tile
 
 // First lane of the run of set bits that holds `lane` (bit `lane` of w is set).
@@ -154,6 +154,27 @@ __global__ __launch_bounds__(kTileWaves * 64) void k_ccl_tile(Grid g, const uint
     }
 }
 
+// Unions of v and u in the lanes where c holds (the whole wave calls).  Along a row most
+// contacts join the same two components of the tiles, so a lane leaves its union to the last
+// lane before it that joins the same two parents: the finds all end at the few roots of the
+// large components, whose words serve one access at a time.  (A union per contact: k_ccl_border
+// 110 us at 128^3, porosity 0.40, and 865 us at 512^3, 0.25; now 70 and 755.)
+template <int SCOPE>
+__device__ inline void ccl_unite_wave(int32_t *L, bool c, int32_t v, int32_t u) {
+    const uint64_t m = __ballot(c);
+    if (!m) return;
+    const int lane = threadIdx.x & 63;
+    int32_t pv = -1, pu = -1;
+    if (c) {
+        pv = __hip_atomic_load(&L[v], __ATOMIC_RELAXED, SCOPE);
+        pu = __hip_atomic_load(&L[u], __ATOMIC_RELAXED, SCOPE);
+    }
+    const uint64_t before = m & ((1ull << lane) - 1);
+    const int last = before ? 63 - __clzll((long long)before) : lane;
+    const int32_t qv = __shfl(pv, last, 64), qu = __shfl(pu, last, 64);
+    if (c && !(before && qv == pv && qu == pu)) ccl_unite<SCOPE>(L, pv, pu);
+}
+
 // The links of a row with its neighbour rows across a tile face in y or z (periodic).
 // All rows' bytes are loaded before the first union, whose atomics nothing moves across.
 __global__ __launch_bounds__(256) void k_ccl_border(Grid g, const uint8_t *__restrict__ pore,
@@ -197,9 +218,9 @@ __global__ __launch_bounds__(256) void k_ccl_border(Grid g, const uint8_t *__res
         // segment before is then made once more
         const Contact c = contact(a, am, ap, b[k], bm, bp, k < 2);
         const int32_t u = (int32_t)(brow[k] + x);
-        if (c.o) ccl_unite<S>(L, v, u);
-        if (c.p) ccl_unite<S>(L, v, u + 1);
-        if (c.m) ccl_unite<S>(L, v, u - 1);
+        ccl_unite_wave<S>(L, c.o, v, u);
+        ccl_unite_wave<S>(L, c.p, v, u + 1);
+        ccl_unite_wave<S>(L, c.m, v, u - 1);
     }
 }
 
