@@ -47,7 +47,9 @@ lbm_status lbm_nn_conv3d(const int32_t n[3], const uint16_t *x, int32_t x_cs, in
                          const uint16_t *w, const float *bias, uint16_t *y, int32_t y_cs,
                          int32_t cout, int32_t flags, void *stream);
 
-/* Workspace bytes of lbm_nn_conv3d_wgrad for this grid and channel counts. */
+/* Workspace bytes of lbm_nn_conv3d_wgrad for this grid and channel counts.  A larger
+ * workspace may be split into more partial sums: the gradients then differ in the order of
+ * summation. */
 size_t lbm_nn_wgrad_workspace(const int32_t n[3], int32_t cin, int32_t cout);
 
 /* Weight and bias gradients of a convolution given its input x and the gradient g of
