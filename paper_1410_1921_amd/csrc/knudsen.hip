@@ -99,6 +99,7 @@ struct KnWs {
     Shift *trans;      // shifts from the current frame to the other one
     uint64_t *halo;    // packets of the resident sweeps [2][kResSlots]
     uint2 *sends;      // their send lists [kResGroups][kResOut]
+    int *n_sends;      // entries of each [kResGroups]
     int *abort;        // set by a resident sweep that gave up
     double *part;      // plane-mean partial sums [nx][kPlaneParts][2]
     double *fpart;     // link-plane flux partial sums [nx + 1][kPlaneParts]
@@ -131,6 +132,7 @@ static KnWs carve_kn(void *base, const Grid &g, int64_t nf, int q) {
     w.samp_out = reinterpret_cast<double *>(w.halo);
     static_assert(2 * kResSlots >= (int64_t)kKnSampleMax * 20, "the samples fit the packets");
     w.sends = c.take<uint2>((size_t)kResGroups * kResOut);
+    w.n_sends = c.take<int>(kResGroups);
     w.abort = c.take<int>(1);
     w.samp_flag = c.take<uint8_t>(kKnSampleMax);
     for (int f = 0; f < 2; f++) w.ref[f] = c.take<double>(kMaxEdge + 2);
@@ -330,8 +332,8 @@ struct Res7 {
     const Shift *__restrict__ shift;  // steady (t0 = 0)
     uint64_t *halo;
     uint2 *sends;
+    int *n_sends;
     int *abort;
-    uint32_t *slots;  // k_res_slots: [6][stride], the packet slot of a pull (in dst)
     int threads, steps;
     uint32_t tag0;
     uint64_t limit;
@@ -359,11 +361,19 @@ __device__ inline int resident_links(const Res7 &a, int64_t lo, int64_t hi, Loca
     return cnt;
 }
 
-// The slot of each pull from another workgroup, for the workgroup that sends it.  More
-// links than a thread has slots for, or a workgroup than its senders take (it sends as many
-// populations as it pulls), give the resident sweep up before it starts.
+// The send lists: where a population that crosses lies in its workgroup's LDS, and the byte
+// offset of the packet slot it goes to (32 bits beside a scalar base: with a 64-bit address
+// formed for every packet a 128^3 step took 0.9 us more).  Neither depends on the buffer or the
+// frame, so they are formed once a solve, in two kernels and memory that no sweep writes: a
+// launch's workgroups meet only by their packets, so whatever one of them reads in its setup may
+// not lie where another one writes its results.
+//
+// k_res_slots: slots[6][stride], the slot of each pull from another workgroup, for the
+// workgroup that sends it.  More links than a thread has slots for, or a workgroup than its
+// senders take (it sends as many populations as it pulls), give the resident sweep up before
+// it starts.
 template <int NPT>
-__global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a) {
+__global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a, uint32_t *__restrict__ slots) {
     __shared__ int total;
     const int bd = a.threads;
     const int64_t lo = (int64_t)blockIdx.x * NPT * bd;
@@ -374,7 +384,8 @@ __global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a) {
         a, lo, hi, [](int, int, int, int) {},
         [&](int r, int, int i, int, int64_t n) {
             if (r < kResLinks)
-                a.slots[(i - 1) * a.stride + n] = ((uint32_t)blockIdx.x * kResLinks + r) * bd + threadIdx.x;
+                slots[(i - 1) * a.stride + n] =
+                    (((uint32_t)blockIdx.x * kResLinks + r) * bd + threadIdx.x) * (uint32_t)sizeof(uint64_t);
         });
     atomicAdd(&total, cnt);
     __syncthreads();
@@ -382,45 +393,72 @@ __global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a) {
         __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Each link the other way: node n's population OPP[i] goes to node id; the active lanes'
+// entries side by side.
+template <int NPT>
+__global__ __launch_bounds__(kResThreads) void k_res_sends(Res7 a, const uint32_t *__restrict__ slots) {
+    LBM_D3Q7_TABLES
+    __shared__ int total;
+    if (*a.abort) return;  // uniform: the lists would not hold the links
+    const int bd = a.threads, tid = threadIdx.x, L = NPT * bd;
+    const int64_t lo = (int64_t)blockIdx.x * L, hi = lo + L < a.nf ? lo + L : a.nf;
+    uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
+    if (tid == 0) total = 0;
+    __syncthreads();
+    resident_links<NPT>(
+        a, lo, hi, [](int, int, int, int) {},
+        [&](int, int j, int i, int id, int64_t) {
+            const uint64_t act = __ballot(1);
+            const int rank = __popcll(act & ((1ull << (tid & 63)) - 1));
+            int base = 0;
+            if (rank == 0) base = atomicAdd(&total, __popcll(act));
+            base = __builtin_amdgcn_readfirstlane(base);
+            sends[base + rank] = uint2{(uint32_t)((OPP[i] - 1) * L + j * bd + tid),
+                                       slots[(OPP[i] - 1) * a.stride + id]};
+        });
+    __syncthreads();
+    if (tid == 0) a.n_sends[blockIdx.x] = total;
+}
+
 template <int NPT>
 __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a) {
     LBM_D3Q7_TABLES
     constexpr int S = __HIP_MEMORY_SCOPE_AGENT;
     __shared__ float lds[(6 * NPT + kResLinks) * kResThreads + 1];
-    __shared__ int quit, total;
+    __shared__ int quit;
     const int bd = a.threads, tid = threadIdx.x, L = NPT * bd;
     const int64_t lo = (int64_t)blockIdx.x * L, hi = lo + L < a.nf ? lo + L : a.nf;
     // population i of local node l at (i - 1) L + l, the thread's packets at 6 L + r bd +
     // tid, and a zero (the deviation of a ghost plane)
     const int in0 = 6 * L + tid, zero = (6 * NPT + kResLinks) * bd;
     if (tid == 0) {
-        quit = total = 0;
+        quit = 0;
         lds[zero] = 0.f;
     }
     __syncthreads();
-    uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
     if (tid >= bd) {  // uniform per wave: the senders
-        __syncthreads();  // the lists are complete
-        const int q = tid - bd, n = total;
+        const uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
+        const int q = tid - bd, n = a.n_sends[blockIdx.x];
         uint32_t from[kResSends], to[kResSends];
 #pragma unroll
         for (int e = 0; e < kResSends; e++) {
             const uint2 w = e * kResSenders + q < n ? sends[e * kResSenders + q] : uint2{0u, 0u};
             from[e] = w.x;
-            to[e] = min(w.y, (uint32_t)kResSlots - 1u);
+            to[e] = w.y;
         }
+        __syncthreads();  // the populations are in place
         for (int t = 0; t < a.steps; t++) {
             __syncthreads();  // every source is read
             if (quit) return;
             __syncthreads();  // the new populations of nodes with links are in place
             if (t + 1 < a.steps) {
                 const uint64_t tag = (uint64_t)(a.tag0 + (uint32_t)t) << 32;
-                uint64_t *__restrict__ halo = a.halo + (t & 1) * kResSlots;
+                gchar *const halo = array_base(a.halo + (t & 1) * kResSlots);
 #pragma unroll
                 for (int e = 0; e < kResSends; e++)
                     if (e * kResSenders + q < n)
-                        __hip_atomic_store(&halo[to[e]], tag | __float_as_uint(lds[from[e]]),
-                                           __ATOMIC_RELAXED, S);
+                        __hip_atomic_store((gptr<uint64_t>)(halo + here(to[e])),
+                                           tag | __float_as_uint(lds[from[e]]), __ATOMIC_RELAXED, S);
             }
             __syncthreads();  // all new populations are in place
         }
@@ -447,22 +485,12 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
             if (i == 2 && id != -1 && lo + l < hi) c2[j] = a.shift[x + 1].tp;
         },
         [&](int r, int j, int i, int id, int64_t n) {
-            const int l = j * bd + tid;
             set_code(j, i, in0 + r * bd);
             linked |= 1 << j;
             lds[in0 + r * bd] = a.src[popq(7, i, id)];  // the first step needs no packet
             const uint32_t x = a.coords[n] & 1023u;
             if (i == 1) c1[j] = a.shift[x + 1].tm;
             if (i == 2) c2[j] = a.shift[x + 1].tp;
-            // the same link the other way: this node's population OPP[i] goes to node id;
-            // the active lanes' entries side by side
-            const uint64_t act = __ballot(1);
-            const int rank = __popcll(act & ((1ull << (tid & 63)) - 1));
-            int base = 0;
-            if (rank == 0) base = atomicAdd(&total, __popcll(act));
-            base = __builtin_amdgcn_readfirstlane(base);
-            sends[base + rank] = uint2{(uint32_t)((OPP[i] - 1) * L + l),
-                                       a.slots[(OPP[i] - 1) * a.stride + id]};
         });
 #pragma unroll
     for (int j = 0; j < NPT; j++) {
@@ -1109,6 +1137,7 @@ static void launch7(const Sweep7 &a, const Variant7 &m, int32_t lattice, hipStre
 
 // Resident sweeps of one solve.
 struct ResPlan {
+    KnTrace *trace = nullptr;
     bool on = false;
     int npt = 1, threads = 64, groups = 1;
     uint32_t tag = 1;    // step numbers used so far in the packets, plus one
@@ -1127,7 +1156,6 @@ constexpr int64_t kResMinSteps = 8;
 // caller left the variant to the library; nodes are spread over all the CUs, at least 256
 // to a workgroup (below that the packets outweigh the nodes).
 static lbm_status resident_plan(int64_t nf, int32_t variant, int32_t lattice, ResPlan &r) {
-    r = ResPlan();
     if (variant != 0 || lattice != LBM_LATTICE_D3Q7 || nf > kResNodes) return LBM_OK;
     int dev = 0, cus = 0, coop = 0;
     LBM_TRY_HIP(hipGetDevice(&dev));
@@ -1158,8 +1186,8 @@ static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift 
     a.shift = steady;
     a.halo = w.halo;
     a.sends = w.sends;
+    a.n_sends = w.n_sends;
     a.abort = w.abort;
-    a.slots = reinterpret_cast<uint32_t *>(w.g[cur ^ 1]);  // 6 of its 7 arrays, until the end
     a.threads = r.threads;
     a.steps = 0;
     a.tag0 = r.tag;
@@ -1167,28 +1195,33 @@ static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift 
     return a;
 }
 
-static lbm_status resident_slots(const Res7 &a, const ResPlan &r, hipStream_t s) {
-    const unsigned nb = (unsigned)r.groups, nt = (unsigned)r.threads;
-    switch (r.npt) {
-    case 1: k_res_slots<1><<<nb, nt, 0, s>>>(a); break;
-    case 2: k_res_slots<2><<<nb, nt, 0, s>>>(a); break;
-    case 3: k_res_slots<3><<<nb, nt, 0, s>>>(a); break;
-    case 4: k_res_slots<4><<<nb, nt, 0, s>>>(a); break;
-    default: k_res_slots<5><<<nb, nt, 0, s>>>(a); break;
-    }
-    LBM_CHECK_LAUNCH();
-    return LBM_OK;
+template <int NPT>
+static void resident_lists(const Res7 &a, const ResPlan &r, uint32_t *slots, hipStream_t s) {
+    k_res_slots<NPT><<<(unsigned)r.groups, (unsigned)r.threads, 0, s>>>(a, slots);
+    k_res_sends<NPT><<<(unsigned)r.groups, (unsigned)r.threads, 0, s>>>(a, slots);
 }
 
-// Whether the lattice's links fit the resident sweeps goes to *w.abort (0: they do), for
-// the caller to read at its next synchronisation; `cur` holds the state.
-static lbm_status resident_probe(const KnWs &w, const Grid &g, int64_t nf, int cur, const ResPlan &r,
+// Readies a solve's resident sweeps: cleared packets and the send lists.  Whether the
+// lattice's links fit goes to *w.abort (0: they do), for the caller to read at its next
+// synchronisation.  `cur` holds the state; the other buffer, which no sweep has written yet,
+// holds the slots between the two kernels.
+static lbm_status resident_setup(const KnWs &w, const Grid &g, int64_t nf, int cur, const ResPlan &r,
                                  hipStream_t s) {
     k_res_flag<<<1, 1, 0, s>>>(w.abort);
     LBM_CHECK_LAUNCH();
     k_res_clear<<<512, 256, 0, s>>>(w.halo, (int64_t)r.groups * r.threads * kResLinks);
     LBM_CHECK_LAUNCH();
-    return resident_slots(resident_args(w, g, nf, nullptr, cur, r), r, s);
+    const Res7 a = resident_args(w, g, nf, nullptr, cur, r);
+    uint32_t *slots = reinterpret_cast<uint32_t *>(w.g[cur ^ 1]);  // 6 of its 7 arrays
+    switch (r.npt) {
+    case 1: resident_lists<1>(a, r, slots, s); break;
+    case 2: resident_lists<2>(a, r, slots, s); break;
+    case 3: resident_lists<3>(a, r, slots, s); break;
+    case 4: resident_lists<4>(a, r, slots, s); break;
+    default: resident_lists<5>(a, r, slots, s); break;
+    }
+    LBM_CHECK_LAUNCH();
+    return LBM_OK;
 }
 
 // `steps` resident sweeps in the frame of `steady` from buffer cur to the other one.
@@ -1199,8 +1232,8 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
     r.tag += (uint32_t)steps;
     r.cur = cur;
     r.steps = steps;
-    const lbm_status st = resident_slots(a, r, s);
-    if (st != LBM_OK) return st;
+    r.trace->launches++;
+    r.trace->resident_steps += steps;
     const void *kernel = r.npt == 1   ? reinterpret_cast<const void *>(&k_resident7<1>)
                          : r.npt == 2 ? reinterpret_cast<const void *>(&k_resident7<2>)
                          : r.npt == 3 ? reinterpret_cast<const void *>(&k_resident7<3>)
@@ -1212,6 +1245,8 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
                                    dim3((unsigned)(r.threads + kResSenders)), args, 0, s) != hipSuccess) {
         (void)hipGetLastError();
         r.on = false;
+        r.trace->refused++;
+        r.trace->resident_steps -= steps;
     }
     return LBM_OK;
 }
@@ -1310,11 +1345,10 @@ static void kn_result(lbm_knudsen_result *r, const lbm_knudsen_params *p, const 
 
 using namespace lbm;
 
-extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid,
-                                        const double *pore_diam, const lbm_knudsen_params *p,
-                                        lbm_knudsen_result *r, float *c_field, const float *c_init,
-                                        double *plane_flux_h, void *workspace, size_t ws_bytes,
-                                        void *stream) {
+static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const double *pore_diam,
+                                const lbm_knudsen_params *p, lbm_knudsen_result *r, float *c_field,
+                                const float *c_init, double *plane_flux_h, void *workspace,
+                                size_t ws_bytes, void *stream, KnTrace &trace) {
     LBM_REQUIRE(n, LBM_E_INVAL, "null size");
     LBM_REQUIRE(n[0] >= 1 && n[1] >= 1 && n[2] >= 1 && n[0] <= kMaxEdge && n[1] <= kMaxEdge &&
                     n[2] <= kMaxEdge,
@@ -1407,11 +1441,12 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
     st = reduce_partials(w.partials, kn_blocks(nf), 1, w.res + 8, s);
     if (st != LBM_OK) return st;
     ResPlan res;
+    res.trace = &trace;
     st = resident_plan(nf, p->variant, h.lattice, res);
     if (st != LBM_OK) return st;
     int too_many = 0;
     if (res.on) {
-        st = resident_probe(w, g, nf, cur, res, s);
+        st = resident_setup(w, g, nf, cur, res, s);
         if (st != LBM_OK) return st;
         LBM_TRY_HIP(hipMemcpyAsync(&too_many, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
     }
@@ -1477,6 +1512,8 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
             // the resident sweep gave up: its start, the frame and the snapshot are as they
             // were (the check did nothing), so plain sweeps run its steps and the check
             res.on = false;
+            res.trace->gave_up++;
+            res.trace->resident_steps -= res.steps;
             cur = res.cur;
             pending = false;
             out = kn_launch(w, g, nf, h, mode, cur, pending, res.steps + 1, true, c_field, &res, s);
@@ -1536,6 +1573,27 @@ extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid
     if (p->fixed_steps > 0 || converged) return LBM_OK;
     set_error("Knudsen solve not converged after %lld steps (residual %.3e)", (long long)t, resid);
     return LBM_W_NOT_CONVERGED;
+}
+
+extern "C" lbm_status lbm_knudsen_solve(const int32_t n[3], const uint8_t *fluid,
+                                        const double *pore_diam, const lbm_knudsen_params *p,
+                                        lbm_knudsen_result *r, float *c_field, const float *c_init,
+                                        double *plane_flux_h, void *workspace, size_t ws_bytes,
+                                        void *stream) {
+    KnTrace trace;
+    return knudsen_solve(n, fluid, pore_diam, p, r, c_field, c_init, plane_flux_h, workspace, ws_bytes,
+                         stream, trace);
+}
+
+extern "C" lbm_status lbm_knudsen_solve_traced(const int32_t n[3], const uint8_t *fluid,
+                                               const double *pore_diam, const lbm_knudsen_params *p,
+                                               lbm_knudsen_result *r, float *c_field,
+                                               const float *c_init, double *plane_flux_h,
+                                               void *workspace, size_t ws_bytes, void *stream,
+                                               lbm::KnTrace *trace_h) {
+    LBM_REQUIRE(trace_h, LBM_E_INVAL, "lbm_knudsen_solve_traced: null trace");
+    return knudsen_solve(n, fluid, pore_diam, p, r, c_field, c_init, plane_flux_h, workspace, ws_bytes,
+                         stream, *trace_h);
 }
 
 static lbm_status read_kn_state(void *workspace, size_t ws_bytes, hipStream_t s, KnHeader &h,
