@@ -606,7 +606,7 @@ __global__ __launch_bounds__(256) void k_res_clear(uint64_t *__restrict__ halo, 
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * used; i += (int64_t)gridDim.x * 256)
         halo[i < used ? i : kResSlots + (i - used)] = 0;
 }
-__global__ void k_res_flag(int *abort) { *abort = 0; }
+__global__ void k_res_flag(int *flag) { *flag = 0; }
 
 // ---------------------------------------------------------------- D3Q19 diffusion
 // The same update on the paper's D3Q19 lattice (Section 3.2): 18 pull sources through the
@@ -1145,9 +1145,6 @@ struct ResPlan {
     int64_t steps = 0;   // with plain sweeps when it gave up
 };
 
-// Longest wait for a packet: 0.2 s of the 100 MHz clock (a step takes microseconds; work
-// of other streams may hold a CU back for a while).
-constexpr uint64_t kResLimit = 20000000;
 // A launch pays for its setup (rank lookups, filling and emptying the LDS: the time of
 // about three plain sweeps).
 constexpr int64_t kResMinSteps = 8;
@@ -1191,7 +1188,7 @@ static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift 
     a.threads = r.threads;
     a.steps = 0;
     a.tag0 = r.tag;
-    a.limit = kResLimit;
+    a.limit = (uint64_t)r.trace->wait_ticks;
     return a;
 }
 
@@ -1234,6 +1231,10 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
     r.steps = steps;
     r.trace->launches++;
     r.trace->resident_steps += steps;
+    if (r.trace->give_up_at == r.trace->launches) {  // the first workgroup sends nothing
+        k_res_flag<<<1, 1, 0, s>>>(w.n_sends);
+        LBM_CHECK_LAUNCH();
+    }
     const void *kernel = r.npt == 1   ? reinterpret_cast<const void *>(&k_resident7<1>)
                          : r.npt == 2 ? reinterpret_cast<const void *>(&k_resident7<2>)
                          : r.npt == 3 ? reinterpret_cast<const void *>(&k_resident7<3>)
@@ -1241,7 +1242,8 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
                                       : reinterpret_cast<const void *>(&k_resident7<5>);
     void *args[] = {&a};
     // refused (fewer compute units than the device names, say): plain sweeps do the steps
-    if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
+    if (r.trace->refuse_at == r.trace->launches ||
+        hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
                                    dim3((unsigned)(r.threads + kResSenders)), args, 0, s) != hipSuccess) {
         (void)hipGetLastError();
         r.on = false;

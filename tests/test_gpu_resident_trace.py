@@ -1,7 +1,8 @@
 """What the resident Knudsen sweeps did, from the trace of the solve: they take the steps they
 are meant to take, also where workgroups share no links (parts of the pore space that do not
-meet) or are many links apart, so that nothing but the packets orders them.  Fields against one
-launch per step, bit for bit."""
+meet) or are many links apart, so that nothing but the packets orders them; and where one gives up a wait,
+or the runtime refuses its launch, plain sweeps take its steps.  Fields against one launch per
+step, bit for bit."""
 import ctypes as C
 
 import numpy as np
@@ -17,7 +18,8 @@ PLAIN = lbm.LBM_VARIANT_EXPLICIT  # an explicit variant is one launch per step
 
 
 class Trace(C.Structure):
-    _fields_ = [("resident_steps", C.c_int64), ("launches", C.c_int32), ("gave_up", C.c_int32),
+    _fields_ = [("wait_ticks", C.c_int64), ("give_up_at", C.c_int32), ("refuse_at", C.c_int32),
+                ("resident_steps", C.c_int64), ("launches", C.c_int32), ("gave_up", C.c_int32),
                 ("refused", C.c_int32), ("pad", C.c_int32)]
 
 
@@ -36,8 +38,8 @@ class Traced:
 
 @pytest.fixture
 def traced(monkeypatch):
-    def solve(*a, **kw):
-        t, lib = Trace(), lbm.load()
+    def solve(*a, wait=20_000_000, give_up_at=0, refuse_at=0, **kw):
+        t, lib = Trace(wait, give_up_at, refuse_at), lbm.load()
         with monkeypatch.context() as m:
             m.setattr(lbm, "load", lambda: Traced(lib, t))
             return lbm.lbm_knudsen_solve(*a, **kw), t
@@ -96,3 +98,51 @@ def test_leaves_what_does_not_fit(traced, shape, p):
     g, d, c0 = inputs(m, 1)
     _, t = traced(g, d, fixed_steps=60, check_every=50, c_init=c0, voxel_nm=2.0)
     assert (t.resident_steps, t.launches, t.gave_up, t.refused) == (0, 0, 0, 0)
+
+
+def same(a, b, m, seed):
+    assert torch.equal(a.field, b.field)
+    for n in ("steps", "converged", "Deff_lattice", "residual", "sum_c", "phi_in", "flux_spread"):
+        assert a[n] == b[n], n
+    nodes = np.flatnonzero(m.reshape(-1))
+    vox = nodes[np.random.default_rng(seed).integers(0, len(nodes), 3000)]
+    for x, y in zip(lbm.lbm_knudsen_sample(a.workspace, vox), lbm.lbm_knudsen_sample(b.workspace, vox)):
+        assert np.array_equal(x, y)
+
+
+# the launch that fails: the first of the solve (it follows the sweep that enters the first
+# frame), a later one, and the last of a solve that ends inside an interval
+@pytest.mark.parametrize("how", ["give_up_at", "refuse_at"])
+@pytest.mark.parametrize("at", [1, 2, 4])
+@pytest.mark.parametrize("shape,p", [((40, 41, 42), 0.5), ((96, 100, 90), 0.40)])
+def test_plain_sweeps_take_over(traced, shape, p, at, how):
+    m = W.blob_mask(shape, p, sum(shape))
+    g, d, c0 = inputs(m, at)
+    steps, every = 165, 50
+    kw = dict(fixed_steps=steps, check_every=every, want_c=True, c_init=c0, voxel_nm=2.0)
+    print(shape, p, how, at, flush=True)
+    a = lbm.lbm_knudsen_solve(g, d, variant=PLAIN, **kw)
+    b, t = traced(g, d, wait=100_000, **{how: at}, **kw)  # 1 ms: the packets never come
+    assert (t.launches, t.gave_up, t.refused) == (at, int(how == "give_up_at"), int(how == "refuse_at"))
+    assert t.resident_steps == (at - 1) * (every - 2)
+    same(a, b, m, at)
+    # on from either, now without a frame to enter before the first resident sweep
+    kw.update(fixed_steps=every + 30, c_init=None, resume=True)
+    q = lbm.lbm_knudsen_solve(g, d, variant=PLAIN, workspace=a.workspace, **kw)
+    r, t = traced(g, d, workspace=b.workspace, wait=100_000, **{how: 1}, **kw)
+    assert (t.launches, t.gave_up + t.refused, t.resident_steps) == (1, 1, 0)
+    same(q, r, m, at)
+
+
+def test_converges_at_the_same_step(traced):
+    m = W.blob_mask((40, 41, 42), 0.7, 11)
+    g, d, _ = inputs(m, 2)
+    kw = dict(tol=3e-4, check_every=50, max_steps=20_000, want_c=True, voxel_nm=2.0)
+    a = lbm.lbm_knudsen_solve(g, d, variant=PLAIN, **kw)
+    assert a["converged"] and 300 < a["steps"]
+    b, t = traced(g, d, **kw)
+    assert (t.gave_up, t.refused) == (0, 0) and t.resident_steps == a["steps"] // 50 * 48
+    same(a, b, m, 3)
+    b, t = traced(g, d, wait=100_000, give_up_at=3, **kw)
+    assert (t.gave_up, t.refused) == (1, 0) and t.resident_steps == 2 * 48
+    same(a, b, m, 3)
