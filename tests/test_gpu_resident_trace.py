@@ -4,6 +4,7 @@ meet) or are many links apart, so that nothing but the packets orders them; and 
 or the runtime refuses its launch, plain sweeps take its steps.  Fields against one launch per
 step, bit for bit."""
 import ctypes as C
+import threading
 
 import numpy as np
 import pytest
@@ -146,3 +147,39 @@ def test_converges_at_the_same_step(traced):
     b, t = traced(g, d, wait=100_000, give_up_at=3, **kw)
     assert (t.gave_up, t.refused) == (1, 0) and t.resident_steps == 2 * 48
     same(a, b, m, 3)
+
+
+def test_beside_other_streams():
+    """Solves on streams of their own, from threads of their own, beside one another and beside a
+    flow solve that keeps the chip busy: the results of the same solves alone."""
+    m = W.blob_mask((96, 100, 90), 0.40, 5)
+    cases = [inputs(m, k) for k in range(3)]
+    kw = dict(fixed_steps=110, check_every=50, want_c=True, voxel_nm=2.0)
+
+    def knudsen(g, d, c0):
+        return [lbm.lbm_knudsen_solve(g, d, c_init=c0, **kw).field for _ in range(6)]
+
+    def flow(g, _d, _c0):
+        return [lbm.lbm_flow_solve(g, fixed_steps=300, want_u=True).field for _ in range(4)]
+
+    jobs = [(knudsen, *cases[0]), (knudsen, *cases[1]), (flow, *cases[2])]
+    alone = [f(*a) for f, *a in jobs]
+    torch.cuda.synchronize()
+    out, start = [None] * len(jobs), threading.Barrier(len(jobs))
+
+    def work(k):
+        f, *a = jobs[k]
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            start.wait()
+            out[k] = f(*a)
+            s.synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for a, b in zip(alone, out):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
