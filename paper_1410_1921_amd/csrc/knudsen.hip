@@ -76,8 +76,13 @@ constexpr int kResNpt = 5;
 constexpr int kResLinks = 12;
 constexpr int kResSends = 32;
 constexpr int64_t kResNodes = (int64_t)kResGroups * kResThreads * kResNpt;
-constexpr int64_t kResSlots = (int64_t)kResGroups * kResThreads * kResLinks;
 constexpr int kResOut = kResSenders * kResSends;
+// Workgroups, and threads of all of them, that a lattice of nf nodes may be cut into (a
+// workgroup but the last holds at least 256 nodes, and a node at least for every thread).
+static int64_t res_groups(int64_t nf) { return std::min<int64_t>((nf + 255) / 256, kResGroups); }
+static int64_t res_threads(int64_t nf) {
+    return std::min<int64_t>(nf + kResThreads, (int64_t)kResGroups * kResThreads);
+}
 
 struct KnWs {
     KnHeader *hdr;
@@ -97,9 +102,9 @@ struct KnWs {
     double *ref[2];    // the two reference profiles, index x + 1 for x = -1..nx
     Shift *steady[2];  // shifts within each frame (t0 = 0)
     Shift *trans;      // shifts from the current frame to the other one
-    uint64_t *halo;    // packets of the resident sweeps [2][kResSlots]
-    uint2 *sends;      // their send lists [kResGroups][kResOut]
-    int *n_sends;      // entries of each [kResGroups]
+    uint64_t *halo;    // packets of the resident sweeps [2][threads kResLinks]
+    uint2 *sends;      // their send lists [groups][kResOut]
+    int *n_sends;      // entries of each
     int *abort;        // set by a resident sweep that gave up
     double *part;      // plane-mean partial sums [nx][kPlaneParts][2]
     double *fpart;     // link-plane flux partial sums [nx + 1][kPlaneParts]
@@ -127,12 +132,14 @@ static KnWs carve_kn(void *base, const Grid &g, int64_t nf, int q) {
     w.total = c.take<int32_t>(1);
     w.rank = c.take<RankWord>(g.nsegs());
     w.samp_vox = c.take<int64_t>(kKnSampleMax);
-    // the packets of the resident sweeps and the samples are never held at once
-    w.halo = c.take<uint64_t>(2 * (size_t)kResSlots);
-    w.samp_out = reinterpret_cast<double *>(w.halo);
-    static_assert(2 * kResSlots >= (int64_t)kKnSampleMax * 20, "the samples fit the packets");
-    w.sends = c.take<uint2>((size_t)kResGroups * kResOut);
-    w.n_sends = c.take<int>(kResGroups);
+    // what the resident sweeps of a solve need lies with the samples: never held at once
+    Carver samples = c;
+    w.samp_out = samples.take<double>((size_t)kKnSampleMax * 20);
+    const bool res = q == 7 && nf <= kResNodes;
+    w.halo = c.take<uint64_t>(res ? 2 * kResLinks * res_threads(nf) : 0);
+    w.sends = c.take<uint2>(res ? res_groups(nf) * kResOut : 0);
+    w.n_sends = c.take<int>(res ? res_groups(nf) : 0);
+    c.off = std::max(c.off, samples.off);
     w.abort = c.take<int>(1);
     w.samp_flag = c.take<uint8_t>(kKnSampleMax);
     for (int f = 0; f < 2; f++) w.ref[f] = c.take<double>(kMaxEdge + 2);
@@ -154,7 +161,11 @@ static KnWs carve_kn(void *base, const Grid &g, int64_t nf, int q) {
 
 size_t knudsen_ws_bytes_n(const int32_t n[3], int64_t nf, int q) {
     Grid g = make_grid(n);
-    return carve_kn(nullptr, g, nf < 0 ? g.nvox() : nf, q).bytes;
+    if (nf < 0) nf = g.nvox();
+    // enough for any lattice of up to nf nodes, the resident sweeps' part with it
+    size_t bytes = carve_kn(nullptr, g, nf, q).bytes;
+    if (q == 7 && nf > kResNodes) bytes = std::max(bytes, carve_kn(nullptr, g, kResNodes, q).bytes);
+    return bytes;
 }
 
 struct Sweep7 {
@@ -334,6 +345,7 @@ struct Res7 {
     uint2 *sends;
     int *n_sends;
     int *abort;
+    int64_t set;  // packet slots of a set
     int threads, steps;
     uint32_t tag0;
     uint64_t limit;
@@ -453,7 +465,7 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
             __syncthreads();  // the new populations of nodes with links are in place
             if (t + 1 < a.steps) {
                 const uint64_t tag = (uint64_t)(a.tag0 + (uint32_t)t) << 32;
-                gchar *const halo = array_base(a.halo + (t & 1) * kResSlots);
+                gchar *const halo = array_base(a.halo + (t & 1) * a.set);
 #pragma unroll
                 for (int e = 0; e < kResSends; e++)
                     if (e * kResSenders + q < n)
@@ -542,7 +554,7 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
             }
         if (t > 0) {
             const uint32_t tag = a.tag0 + (uint32_t)(t - 1);
-            const uint64_t *__restrict__ halo = a.halo + ((t - 1) & 1) * kResSlots + in_slot;
+            const uint64_t *__restrict__ halo = a.halo + ((t - 1) & 1) * a.set + in_slot;
             uint64_t since = 0;
 #pragma unroll
             for (int r0 = 0; r0 < kResLinks; r0 += 4) {  // four packets in flight
@@ -601,10 +613,9 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
     }
 }
 
-// Clears the step numbers of the packets a solve uses, in both sets.
-__global__ __launch_bounds__(256) void k_res_clear(uint64_t *__restrict__ halo, int64_t used) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * used; i += (int64_t)gridDim.x * 256)
-        halo[i < used ? i : kResSlots + (i - used)] = 0;
+// Clears the step numbers of a solve's packets.
+__global__ __launch_bounds__(256) void k_res_clear(uint64_t *__restrict__ halo, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) halo[i] = 0;
 }
 __global__ void k_res_flag(int *flag) { *flag = 0; }
 
@@ -1165,7 +1176,7 @@ static lbm_status resident_plan(int64_t nf, int32_t variant, int32_t lattice, Re
     if (r.npt > kResNpt) return LBM_OK;
     r.threads = (int)((per + r.npt - 1) / r.npt + 63) / 64 * 64;
     r.groups = (int)((nf + (int64_t)r.npt * r.threads - 1) / ((int64_t)r.npt * r.threads));
-    r.on = true;
+    r.on = r.groups <= res_groups(nf) && (int64_t)r.groups * r.threads <= res_threads(nf);
     return LBM_OK;
 }
 
@@ -1185,6 +1196,7 @@ static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift 
     a.sends = w.sends;
     a.n_sends = w.n_sends;
     a.abort = w.abort;
+    a.set = (int64_t)r.groups * r.threads * kResLinks;
     a.threads = r.threads;
     a.steps = 0;
     a.tag0 = r.tag;
@@ -1206,9 +1218,9 @@ static lbm_status resident_setup(const KnWs &w, const Grid &g, int64_t nf, int c
                                  hipStream_t s) {
     k_res_flag<<<1, 1, 0, s>>>(w.abort);
     LBM_CHECK_LAUNCH();
-    k_res_clear<<<512, 256, 0, s>>>(w.halo, (int64_t)r.groups * r.threads * kResLinks);
-    LBM_CHECK_LAUNCH();
     const Res7 a = resident_args(w, g, nf, nullptr, cur, r);
+    k_res_clear<<<512, 256, 0, s>>>(w.halo, 2 * a.set);
+    LBM_CHECK_LAUNCH();
     uint32_t *slots = reinterpret_cast<uint32_t *>(w.g[cur ^ 1]);  // 6 of its 7 arrays
     switch (r.npt) {
     case 1: resident_lists<1>(a, r, slots, s); break;
