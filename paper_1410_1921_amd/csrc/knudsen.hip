@@ -20,6 +20,7 @@
 #include <cstring>
 #include <vector>
 
+#include "knudsen_trace.h"
 #include "lbm_internal.h"
 
 namespace lbm {
