@@ -1457,10 +1457,18 @@ static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const 
     if (st != LBM_OK) return st;
     ResPlan res;
     res.trace = &trace;
-    st = resident_plan(nf, p->variant, h.lattice, res);
-    if (st != LBM_OK) return st;
+    const int64_t limit = p->fixed_steps > 0 ? p->fixed_steps : p->max_steps;
+    const int nc = p->check_every;
+    // the longest run of steps between the sweep that enters a frame and the one that checks:
+    // that of the first interval, or of a later one, each of which enters a frame
+    const int64_t first = std::min<int64_t>(nc - t0 % nc, limit), later = std::min<int64_t>(nc, limit - first);
+    if (std::max(first - (pending ? 2 : 1), later - 2) >= kResMinSteps) {
+        st = resident_plan(nf, p->variant, h.lattice, res);
+        if (st != LBM_OK) return st;
+    }
     int too_many = 0;
     if (res.on) {
+        trace.lists++;
         st = resident_setup(w, g, nf, cur, res, s);
         if (st != LBM_OK) return st;
         LBM_TRY_HIP(hipMemcpyAsync(&too_many, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1493,8 +1501,6 @@ static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const 
     LBM_TRY_HIP(hipEventCreate(&pin.e0));
     LBM_TRY_HIP(hipEventCreate(&pin.e1));
     const hipEvent_t e0 = pin.e0, e1 = pin.e1;
-    const int64_t limit = p->fixed_steps > 0 ? p->fixed_steps : p->max_steps;
-    const int nc = p->check_every;
     double sums[kKnSums] = {0, 0, 0, 0, 0};
     double resid = INFINITY, sweep_ms = 0.0;
     SteadyEst est;

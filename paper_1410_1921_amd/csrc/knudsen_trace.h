@@ -17,7 +17,7 @@ struct KnTrace {
     int32_t launches = 0;        // their launches,
     int32_t gave_up = 0;         // those that gave up a wait (plain sweeps then took their steps),
     int32_t refused = 0;         // and those the runtime refused
-    int32_t pad = 0;
+    int32_t lists = 0;           // times their send lists were formed
 };
 
 }  // namespace lbm

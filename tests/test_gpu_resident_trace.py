@@ -21,7 +21,7 @@ PLAIN = lbm.LBM_VARIANT_EXPLICIT  # an explicit variant is one launch per step
 class Trace(C.Structure):
     _fields_ = [("wait_ticks", C.c_int64), ("give_up_at", C.c_int32), ("refuse_at", C.c_int32),
                 ("resident_steps", C.c_int64), ("launches", C.c_int32), ("gave_up", C.c_int32),
-                ("refused", C.c_int32), ("pad", C.c_int32)]
+                ("refused", C.c_int32), ("lists", C.c_int32)]
 
 
 class Traced:
@@ -183,3 +183,16 @@ def test_beside_other_streams():
     for a, b in zip(alone, out):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("every,first,then", [(8, (0, 0), (0, 0)), (9, (0, 0), (1, 1)), (10, (1, 3), (1, 3))])
+def test_no_lists_for_short_intervals(traced, every, first, then):
+    """(lists formed, launches) from rest and resumed: an interval from rest has two plain sweeps,
+    the first one of a resumed solve only its check."""
+    m = W.blob_mask((40, 41, 42), 0.5, 5)
+    g, d, c0 = inputs(m, 4)
+    kw = dict(fixed_steps=3 * every, check_every=every, voxel_nm=2.0)
+    a, t = traced(g, d, c_init=c0, **kw)
+    assert (t.lists, t.launches) == first
+    _, t = traced(g, d, workspace=a.workspace, resume=True, **kw)
+    assert (t.lists, t.launches) == then
