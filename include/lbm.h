@@ -111,12 +111,12 @@ typedef int32_t lbm_status;
  * (2 included) is rejected with LBM_E_INVAL.  A batched solve without
  * LBM_VARIANT_EXPLICIT chooses the variant of each of its groups from the group's size.
  * Population offsets (direction x stride + node; stride: the fluid-node count rounded up
- * to 256) are 32-bit while they fit, in bytes for the flow (19 x stride x the stored size:
- * 56 M nodes in binary32) and in elements for the mass transport (q x stride, q = 19 or 7),
- * which keeps the sweeps' register and instruction counts down, and 64-bit beyond, so that
- * a 1024^3 domain of any porosity is solved; LBM_VARIANT_OFF64
- * asks for the 64-bit kernels on any size (single-lattice solves, with or without
- * LBM_VARIANT_EXPLICIT; identical results). */
+ * to 256) are 32-bit while they fit, in bytes on D3Q19 (19 x stride x the stored size: 56 M
+ * nodes in binary32, flow and mass transport alike, 28 M in binary64) and in elements on
+ * D3Q7 (7 x stride: 613 M nodes), which keeps the sweeps' register and instruction counts
+ * down, and 64-bit beyond, so that a 1024^3 domain of any porosity is solved;
+ * LBM_VARIANT_OFF64 asks for the 64-bit kernels on any size (single-lattice solves, with or
+ * without LBM_VARIANT_EXPLICIT; identical results). */
 #define LBM_VARIANT_AUTO 0
 #define LBM_VARIANT_EXPLICIT 1
 #define LBM_VARIANT_REMAP 4

@@ -1113,9 +1113,15 @@ struct Variant7 {
     bool wide;  // 64-bit population offsets
 };
 
+// 32-bit population offsets reach the whole lattice: elements for D3Q7, bytes for D3Q19
+// (pop_offset's, with three arrays of 256 on either side).
+static bool narrow7(int64_t stride, int q) {
+    return (q == 19 ? (19 * stride + 6 * 256) * (int64_t)sizeof(float) : q * stride) <= (int64_t)UINT32_MAX;
+}
+
 static Variant7 pick_variant7(int32_t v, int64_t stride, int q = 7) {
     Variant7 m;
-    m.wide = (v & LBM_VARIANT_OFF64) || q * stride > (int64_t)UINT32_MAX;
+    m.wide = (v & LBM_VARIANT_OFF64) || !narrow7(stride, q);
     if (v & LBM_VARIANT_EXPLICIT) {
         m.remap = v & LBM_VARIANT_REMAP;
         m.nt = v & LBM_VARIANT_NTSTORE;
@@ -1141,9 +1147,7 @@ static void launch7o(const Sweep7 &a, const Variant7 &m, int32_t lattice, hipStr
 
 template <bool CHECK>
 static void launch7(const Sweep7 &a, const Variant7 &m, int32_t lattice, hipStream_t s) {
-    // D3Q7 counts elements, D3Q19 bytes (with 3 arrays of margin either side)
-    const int64_t top = lattice == LBM_LATTICE_D3Q19 ? 4 * (19 * a.stride + 6 * 256) : kn_q(lattice) * a.stride;
-    if (m.wide || top > (int64_t)UINT32_MAX) launch7o<CHECK, int64_t>(a, m, lattice, s);
+    if (m.wide) launch7o<CHECK, int64_t>(a, m, lattice, s);
     else launch7o<CHECK, uint32_t>(a, m, lattice, s);
 }
 
