@@ -8,6 +8,7 @@
 // so the [skip, upsampled] concatenation of a decoder input is two views of one buffer.
 // Weights are [27][cout][cin], tap t = 9 (dz + 1) + 3 (dy + 1) + (dx + 1); products
 // accumulate in binary32.
+#include <algorithm>
 #include <type_traits>
 #include <cmath>
 #include <cstdint>
@@ -1271,9 +1272,15 @@ extern "C" lbm_status lbm_nn_make_input(int64_t nvox, const uint8_t *mask, const
     if (nvox == 0) return LBM_OK;
     const int n = vec(x_cs, {}, {x});
     const auto kernel = n == 8 ? k_make_input<8> : n == 4 ? k_make_input<4> : k_make_input<1>;
-    kernel<<<nblk(nvox * (x_cs / n)), 256, 0, static_cast<hipStream_t>(stream)>>>(nvox, mask, diam,
-                                                                                1.0 / d_scale, x, x_cs);
-    LBM_CHECK_LAUNCH();
+    // a launch holds fewer than 2^32 threads: with a thread per group of channels, fewer voxels
+    // than a call may have
+    const int64_t most = std::max<int64_t>((int64_t)0x80000000 / (x_cs / n), 1);
+    for (int64_t v = 0; v < nvox; v += most) {
+        const int64_t nv = std::min(nvox - v, most);
+        kernel<<<nblk(nv * (x_cs / n)), 256, 0, static_cast<hipStream_t>(stream)>>>(
+            nv, mask + v, diam + v, 1.0 / d_scale, x + v * x_cs, x_cs);
+        LBM_CHECK_LAUNCH();
+    }
     return LBM_OK;
 }
 
