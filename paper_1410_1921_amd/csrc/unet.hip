@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void k_conv3d_bricks(NnGrid g, const uint16_t 
     const int sxv = x0 - 1 + hx, syv = y0 - 1 + hy, szv = z0 - 1 + hz;
     const bool inside = hz < PP && sxv >= 0 && sxv < g.nx && syv >= 0 && syv < g.ny;
     // addresses as one scalar base per load and one lane offset for all of them: in 32 bits
-    // where a thread stays in one plane (10 rows of a tensor are far below 2^32 elements)
+    // where a thread stays in one plane (10 rows of a tensor: lbm_nn_conv3d sees to the limit)
     typedef typename std::conditional<PP == 1, uint32_t, int64_t>::type LaneOff;
     const int64_t plane = (int64_t)g.nx * g.ny * x_cs;
     const uint16_t *const src = x + (z0 - 1) * plane + ((int64_t)(y0 - 1) * g.nx + x0 - 1) * x_cs;
@@ -988,9 +988,12 @@ extern "C" lbm_status lbm_nn_conv3d(const int32_t n[3], const uint16_t *x, int32
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int relu = (flags & LBM_NN_RELU) != 0, flip = (flags & LBM_NN_FLIP) != 0;
     // bricks: grid sizes multiples of 4 and 16-byte input rows (the halo is copied as
-    // 16-byte vectors)
+    // 16-byte vectors), with the elements of a halo plane (10 x 10 voxels at most), of a 4 x 4
+    // output plane and of 8 taps' weights within 32-bit offsets
+    const int64_t reach = std::max({(int64_t)9 * (g.nx + 1) * x_cs + 16, (int64_t)3 * (g.nx + 1) * y_cs + 16,
+                                    (int64_t)8 * cout * cin});
     if (g.nx % 4 == 0 && g.ny % 4 == 0 && g.nz % 4 == 0 && x_cs % 8 == 0 &&
-        reinterpret_cast<uintptr_t>(x) % 16 == 0) {
+        reinterpret_cast<uintptr_t>(x) % 16 == 0 && reach <= (int64_t)INT32_MAX) {
         LBM_REQUIRE(cout == 16 || cout == 32 || cout == 48 || cout == 64 || cout == 96 ||
                         cout == 128 || cout == 192,
                     LBM_E_INVAL, "lbm_nn_conv3d: cout %d not supported", cout);

@@ -24,3 +24,32 @@ def test_network_input_beyond_a_launch(nv, cs, off):
         assert not x[:, c].any(), c
     del x
     torch.cuda.empty_cache()
+
+
+# 9 (nx + 1) x_cs and 3 (nx + 1) y_cs on either side of 2^31 at nx = 4: the input rows as 32-bit
+# offsets reach them and beyond; the same for the output rows
+@pytest.mark.parametrize("flags", [0, nn.LBM_NN_FLIP])
+@pytest.mark.parametrize("xcs,ycs", [(47_721_856, 16), (47_721_864, 16), (95_443_720, 16),
+                                     (16, 143_165_568), (16, 143_165_580), (16, 286_331_160)])
+def test_convolution_of_wide_strides(xcs, ycs, flags):
+    """Whole numbers small enough for exact sums in any order, as dense tensors and as views of
+    wide rows; the elements beyond a view are left alone."""
+    shape, nv, cin, cout = (4, 4, 4), 64, 16, 16
+    gen = torch.Generator().manual_seed(7)
+    x = torch.randint(-3, 4, (nv, cin), generator=gen).to(torch.bfloat16).cuda()
+    w = torch.randint(-2, 3, (27 * cin * cout,), generator=gen).to(torch.bfloat16).cuda()
+    bias = torch.randint(-9, 10, (cout,), generator=gen).float().cuda()
+    ref = torch.empty((nv, cout), dtype=torch.bfloat16, device="cuda")
+    nn.lbm_nn_conv3d(shape, View(x), cin, w, bias, View(ref), cout, flags)
+    xw, yw = x, torch.empty((nv, ycs), dtype=torch.bfloat16, device="cuda")
+    if xcs > cin:
+        xw = torch.zeros((nv, xcs), dtype=torch.bfloat16, device="cuda")
+        xw[:, :cin] = x
+    edge = min(ycs, cout + 4)
+    yw[:, :edge] = 7.0
+    print(xcs, ycs, flags, flush=True)
+    nn.lbm_nn_conv3d(shape, View(xw), cin, w, bias, View(yw), cout, flags)
+    assert torch.equal(yw[:, :cout], ref)
+    assert (yw[:, cout:edge] == 7.0).all()
+    del xw, yw
+    torch.cuda.empty_cache()
