@@ -432,7 +432,8 @@ typedef struct {
     double phi_in, phi_out, flux_spread; /* spread = (max - min)/mean of plane fluxes */
     double residual, sum_c;
     double sweep_ms, mlups, gbps;        /* gbps with 60 (D3Q7) or 156 (D3Q19) algorithmic
-                                            bytes per update */
+                                            bytes per update, also of steps that hold the
+                                            lattice on the chip and move few of them */
     double steady_dist;                  /* as in lbm_flow_result, for C */
     double Deff_planes;                  /* Eq. 14 with the mean of the nx + 1 link-plane
                                             fluxes in place of the outlet's: equal to
