@@ -106,7 +106,8 @@ struct KnWs {
     uint64_t *halo;    // packets of the resident sweeps [2][threads kResLinks]
     uint2 *sends;      // their send lists [groups][kResOut]
     int *n_sends;      // entries of each
-    int *abort;        // set by a resident sweep that gave up
+    int *abort;        // [0] set by a resident sweep that gave up, [1] the 64-byte lines that the
+                       // packets of a step are written in, [2] the packets
     double *part;      // plane-mean partial sums [nx][kPlaneParts][2]
     double *fpart;     // link-plane flux partial sums [nx + 1][kPlaneParts]
     int64_t stride;
@@ -141,7 +142,7 @@ static KnWs carve_kn(void *base, const Grid &g, int64_t nf, int q) {
     w.sends = c.take<uint2>(res ? res_groups(nf) * kResOut : 0);
     w.n_sends = c.take<int>(res ? res_groups(nf) : 0);
     c.off = std::max(c.off, samples.off);
-    w.abort = c.take<int>(1);
+    w.abort = c.take<int>(3);
     w.samp_flag = c.take<uint8_t>(kKnSampleMax);
     for (int f = 0; f < 2; f++) w.ref[f] = c.take<double>(kMaxEdge + 2);
     for (int f = 0; f < 2; f++) w.steady[f] = c.take<Shift>(kMaxEdge + 2);
@@ -407,30 +408,41 @@ __global__ __launch_bounds__(kResThreads) void k_res_slots(Res7 a, uint32_t *__r
 }
 
 // Each link the other way: node n's population OPP[i] goes to node id; the active lanes'
-// entries side by side.
+// entries side by side.  The lines and packets of a step are added up in abort[1] and [2].
 template <int NPT>
 __global__ __launch_bounds__(kResThreads) void k_res_sends(Res7 a, const uint32_t *__restrict__ slots) {
     LBM_D3Q7_TABLES
-    __shared__ int total;
+    __shared__ int total, lines;
     if (*a.abort) return;  // uniform: the lists would not hold the links
     const int bd = a.threads, tid = threadIdx.x, L = NPT * bd;
     const int64_t lo = (int64_t)blockIdx.x * L, hi = lo + L < a.nf ? lo + L : a.nf;
     uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
-    if (tid == 0) total = 0;
+    if (tid == 0) total = lines = 0;
     __syncthreads();
     resident_links<NPT>(
         a, lo, hi, [](int, int, int, int) {},
         [&](int, int j, int i, int id, int64_t) {
+            const uint32_t to = slots[(OPP[i] - 1) * a.stride + id];
             const uint64_t act = __ballot(1);
-            const int rank = __popcll(act & ((1ull << (tid & 63)) - 1));
+            const int lane = tid & 63, rank = __popcll(act & ((1ull << lane) - 1));
+            // a line goes on where the lane before writes the slot before in it
+            const uint32_t before = __shfl_up(to, 1, 64);
+            const bool on = lane > 0 && ((act >> (lane - 1)) & 1) && before + 8 == to && to % 64 != 0;
+            const uint64_t starts = __ballot(!on);
             int base = 0;
-            if (rank == 0) base = atomicAdd(&total, __popcll(act));
+            if (rank == 0) {
+                base = atomicAdd(&total, __popcll(act));
+                atomicAdd(&lines, __popcll(starts));
+            }
             base = __builtin_amdgcn_readfirstlane(base);
-            sends[base + rank] = uint2{(uint32_t)((OPP[i] - 1) * L + j * bd + tid),
-                                       slots[(OPP[i] - 1) * a.stride + id]};
+            sends[base + rank] = uint2{(uint32_t)((OPP[i] - 1) * L + j * bd + tid), to};
         });
     __syncthreads();
-    if (tid == 0) a.n_sends[blockIdx.x] = total;
+    if (tid == 0) {
+        a.n_sends[blockIdx.x] = total;
+        atomicAdd(&a.abort[1], lines);
+        atomicAdd(&a.abort[2], total);
+    }
 }
 
 template <int NPT>
@@ -618,7 +630,7 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
 __global__ __launch_bounds__(256) void k_res_clear(uint64_t *__restrict__ halo, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) halo[i] = 0;
 }
-__global__ void k_res_flag(int *flag) { *flag = 0; }
+__global__ void k_res_zero(int *p) { p[threadIdx.x] = 0; }
 
 // ---------------------------------------------------------------- D3Q19 diffusion
 // The same update on the paper's D3Q19 lattice (Section 3.2): 18 pull sources through the
@@ -1156,14 +1168,29 @@ struct ResPlan {
     KnTrace *trace = nullptr;
     bool on = false;
     int npt = 1, threads = 64, groups = 1;
+    int64_t min_steps = 0;  // of a launch
     uint32_t tag = 1;    // step numbers used so far in the packets, plus one
     int cur = 0;         // buffer and steps of the last resident launch: what is run again
     int64_t steps = 0;   // with plain sweeps when it gave up
 };
 
-// A launch pays for its setup (rank lookups, filling and emptying the LDS: the time of
-// about three plain sweeps).
-constexpr int64_t kResMinSteps = 8;
+// Fewest steps of a resident launch, from the microseconds that a step takes either way.  A
+// launch costs 30 to 60 us more than a sweep (its cooperative start, rank lookups, filling and
+// emptying the LDS); a resident step is bound by the exchange, so by the 64-byte lines and the
+// packets of a workgroup, besides its nodes; a plain one by its launch, then by the cache.
+// Measured, plain and resident step, and the interval from which resident is the faster:
+//   20^3, porosity 0.5         3.6, 1.4 us     18 steps
+//   64^3, 0.45                 4.1, 1.8        18
+//   90 x 96 x 100, 0.40        5.6, 2.8        13
+//   128^3, 0.40               10.1, 4.3         8
+//   40 x 40 x 300, 0.5         5.3, 3.8        60 (rows along x: every neighbour row far away)
+//   24 x 24 x 1000, 0.5        5.2, 5.1        none up to 100
+//   16 x 64 x 700, 0.6         6.2, 6.6        none
+static int64_t resident_min_steps(int64_t nf, int groups, double lines, double packets) {
+    const double n = 1e-6 * (double)nf, plain = std::max(3.5 + 5.5 * n, 2.2 + 9.4 * n);
+    const double res = 0.8 + (1.4e-3 * lines + 6e-4 * packets + 3.6e-4 * (double)nf) / groups;
+    return plain - res < 0.1 ? INT64_MAX : std::max<int64_t>(8, (int64_t)std::ceil(50.0 / (plain - res)));
+}
 
 // The resident sweeps are used where the whole lattice fits one workgroup per CU and the
 // caller left the variant to the library; nodes are spread over all the CUs, at least 256
@@ -1221,7 +1248,7 @@ static void resident_lists(const Res7 &a, const ResPlan &r, uint32_t *slots, hip
 // holds the slots between the two kernels.
 static lbm_status resident_setup(const KnWs &w, const Grid &g, int64_t nf, int cur, const ResPlan &r,
                                  hipStream_t s) {
-    k_res_flag<<<1, 1, 0, s>>>(w.abort);
+    k_res_zero<<<1, 3, 0, s>>>(w.abort);
     LBM_CHECK_LAUNCH();
     const Res7 a = resident_args(w, g, nf, nullptr, cur, r);
     k_res_clear<<<512, 256, 0, s>>>(w.halo, 2 * a.set);
@@ -1249,7 +1276,7 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
     r.trace->launches++;
     r.trace->resident_steps += steps;
     if (r.trace->give_up_at == r.trace->launches) {  // the first workgroup sends nothing
-        k_res_flag<<<1, 1, 0, s>>>(w.n_sends);
+        k_res_zero<<<1, 1, 0, s>>>(w.n_sends);
         LBM_CHECK_LAUNCH();
     }
     const void *kernel = r.npt == 1   ? reinterpret_cast<const void *>(&k_resident7<1>)
@@ -1290,7 +1317,7 @@ static lbm_status kn_launch(const KnWs &w, const Grid &g, int64_t nf, KnHeader &
     for (int64_t t = 0; t < steps; t++) {
         // between the sweep that enters a frame and the one that checks: one launch
         const int64_t plain = steps - t - (check_last ? 1 : 0);
-        if (res && res->on && !pending && plain >= kResMinSteps) {
+        if (res && res->on && !pending && plain >= res->min_steps) {
             const lbm_status st = resident_steps(w, g, nf, w.steady[h.frame], cur, plain, *res, s);
             if (st != LBM_OK) return st;
             if (res->on) {
@@ -1466,23 +1493,29 @@ static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const 
     // the longest run of steps between the sweep that enters a frame and the one that checks:
     // that of the first interval, or of a later one, each of which enters a frame
     const int64_t first = std::min<int64_t>(nc - t0 % nc, limit), later = std::min<int64_t>(nc, limit - first);
-    if (std::max(first - (pending ? 2 : 1), later - 2) >= kResMinSteps) {
-        st = resident_plan(nf, p->variant, h.lattice, res);
-        if (st != LBM_OK) return st;
-    }
-    int too_many = 0;
+    const int64_t longest = std::max(first - (pending ? 2 : 1), later - 2);
+    st = resident_plan(nf, p->variant, h.lattice, res);
+    if (st != LBM_OK) return st;
+    const auto min_steps = [&](int lines, int packets) {
+        return trace.min_steps > 0 ? trace.min_steps : resident_min_steps(nf, res.groups, lines, packets);
+    };
+    res.on = res.on && longest >= min_steps(0, 0);
+    int probe[3] = {0, 0, 0};  // too many links, lines, packets
     if (res.on) {
         trace.lists++;
         st = resident_setup(w, g, nf, cur, res, s);
         if (st != LBM_OK) return st;
-        LBM_TRY_HIP(hipMemcpyAsync(&too_many, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+        LBM_TRY_HIP(hipMemcpyAsync(probe, w.abort, sizeof(probe), hipMemcpyDeviceToHost, s));
     }
     unsigned long long bad = 0;
     double sum_tau = 0.0;
     LBM_TRY_HIP(hipMemcpyAsync(&bad, w.counter, sizeof(bad), hipMemcpyDeviceToHost, s));
     LBM_TRY_HIP(hipMemcpyAsync(&sum_tau, w.res + 8, sizeof(double), hipMemcpyDeviceToHost, s));
     LBM_TRY_HIP(hipStreamSynchronize(s));
-    if (too_many) res.on = false;
+    if (res.on) {
+        res.min_steps = min_steps(probe[1], probe[2]);
+        res.on = !probe[0] && longest >= res.min_steps;
+    }
     LBM_REQUIRE(bad == 0, LBM_E_INVAL, "%llu fluid nodes have tau_g <= 1/2 (pore diameter <= 0)", bad);
     if (c_field) LBM_TRY_HIP(hipMemsetAsync(c_field, 0, sizeof(float) * g.nvox(), s));
 

@@ -18,6 +18,8 @@ struct KnTrace {
     int32_t gave_up = 0;         // those that gave up a wait (plain sweeps then took their steps),
     int32_t refused = 0;         // and those the runtime refused
     int32_t lists = 0;           // times their send lists were formed
+    int32_t min_steps = 0;       // > 0: the fewest steps of a launch, instead of the rule's
+    int32_t pad = 0;
 };
 
 }  // namespace lbm

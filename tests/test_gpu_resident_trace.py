@@ -21,7 +21,8 @@ PLAIN = lbm.LBM_VARIANT_EXPLICIT  # an explicit variant is one launch per step
 class Trace(C.Structure):
     _fields_ = [("wait_ticks", C.c_int64), ("give_up_at", C.c_int32), ("refuse_at", C.c_int32),
                 ("resident_steps", C.c_int64), ("launches", C.c_int32), ("gave_up", C.c_int32),
-                ("refused", C.c_int32), ("lists", C.c_int32)]
+                ("refused", C.c_int32), ("lists", C.c_int32), ("min_steps", C.c_int32),
+                ("pad", C.c_int32)]
 
 
 class Traced:
@@ -39,8 +40,8 @@ class Traced:
 
 @pytest.fixture
 def traced(monkeypatch):
-    def solve(*a, wait=20_000_000, give_up_at=0, refuse_at=0, **kw):
-        t, lib = Trace(wait, give_up_at, refuse_at), lbm.load()
+    def solve(*a, wait=20_000_000, give_up_at=0, refuse_at=0, min_steps=8, **kw):
+        t, lib = Trace(wait, give_up_at, refuse_at, min_steps=min_steps), lbm.load()
         with monkeypatch.context() as m:
             m.setattr(lbm, "load", lambda: Traced(lib, t))
             return lbm.lbm_knudsen_solve(*a, **kw), t
@@ -196,3 +197,18 @@ def test_no_lists_for_short_intervals(traced, every, first, then):
     assert (t.lists, t.launches) == first
     _, t = traced(g, d, workspace=a.workspace, resume=True, **kw)
     assert (t.lists, t.launches) == then
+
+
+@pytest.mark.parametrize("shape,p,every,launches", [((20, 20, 20), 0.5, 12, 0), ((20, 20, 20), 0.5, 50, 2),
+                                                    ((128, 128, 128), 0.40, 14, 2),
+                                                    ((16, 64, 700), 0.6, 100, 0), ((24, 24, 1000), 0.5, 100, 0)])
+def test_only_where_it_is_faster(traced, shape, p, every, launches):
+    """The rule's clear cases: short intervals of a small lattice, and boxes whose workgroups have
+    every neighbour row in another one, are left to plain sweeps."""
+    m = W.blob_mask(shape, p, 3)
+    g, d, c0 = inputs(m, 1)
+    kw = dict(fixed_steps=2 * every, check_every=every, want_c=True, c_init=c0, voxel_nm=2.0)
+    a = lbm.lbm_knudsen_solve(g, d, variant=PLAIN, **kw)
+    b, t = traced(g, d, min_steps=0, **kw)
+    assert (t.launches, t.gave_up) == (launches, 0)
+    assert torch.equal(a.field, b.field)
