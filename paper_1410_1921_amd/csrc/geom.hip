@@ -23,6 +23,18 @@ static dim3 row_grid(const Grid &g) {
 }
 constexpr int kRows = 4;
 
+// The distance passes give a wave several rows of a box of up to 32 voxels in x: rows of 2^lane_log
+// lanes each (nx = 1, ny = nz = 1000: 386 us for the three passes with a wave a row, now 20).
+__host__ __device__ inline int lane_log(const Grid &g) {
+    int s = 0;
+    while ((1 << s) < g.nx && s < 6) s++;
+    return s;
+}
+static dim3 lane_grid(const Grid &g) {
+    const int rows = kRows << (6 - lane_log(g));
+    return dim3((unsigned)g.nseg, (unsigned)((g.ny + rows - 1) / rows), (unsigned)g.nz);
+}
+
 // ================================================================ labelling
 // Union-find over the pore voxels.  What bounds it is the chains of dependent loads a
 // find walks, so the trees are kept flat and the unions few:
@@ -527,27 +539,30 @@ __global__ __launch_bounds__(256) void k_chords(Grid g, const uint8_t *__restric
 }
 
 // ================================================================ distance map
-// Squared distance to the nearest solid voxel along x: one wave per row, from the bits
-// of its segments.  (One thread per row, two scans of it, ran 7.7 ms at 512^3 on
+// Squared distance to the nearest solid voxel along x: one wave per row, or several short
+// rows, from the bits of its segments.  (One thread per row, two scans of it, ran 7.7 ms at 512^3 on
 // uncoalesced rows; now 0.28 ms.)
 __global__ __launch_bounds__(256) void k_edt_x(Grid g, const uint8_t *__restrict__ pore,
                                                int32_t *__restrict__ out, int *__restrict__ emax) {
     __shared__ uint64_t solid[kRows][kMaxEdge / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * kRows + wave;
+    const int wave = threadIdx.x >> 6, sh = lane_log(g);
+    const int lane = threadIdx.x & ((1 << sh) - 1), first = (threadIdx.x & 63) - lane;  // of the row
+    const int64_t row = ((int64_t)blockIdx.x * kRows + wave) * (64 >> sh) + (first >> sh);
     if (blockIdx.x == 0 && threadIdx.x == 0) *emax = 0;
-    const bool live = row < (int64_t)g.ny * g.nz;  // uniform per wave
+    const bool live = row < (int64_t)g.ny * g.nz;
     const int64_t base = row * g.nx;
+    uint64_t own = 0;  // the solid bits of a row of one segment
     for (int k = 0; k < g.nseg; k++) {
         const int x = k * 64 + lane;
-        const uint64_t w = __ballot(live && x < g.nx && pore[base + x] == 0);
-        if (lane == 0) solid[wave][k] = w;
+        own = __ballot(live && x < g.nx && pore[base + x] == 0);
+        if ((threadIdx.x & 63) == 0) solid[wave][k] = own;
     }
+    own = own >> first & (~0ull >> (64 - (1 << sh)));
     __syncthreads();
     if (!live) return;
     int left = -kInf;  // last solid before this segment
     for (int k = 0; k < g.nseg; k++) {
-        const uint64_t w = solid[wave][k];
+        const uint64_t w = g.nseg == 1 ? own : solid[wave][k];
         int right = kInf;  // first solid after this segment
         for (int j = k + 1; j < g.nseg; j++) {
             const uint64_t n = solid[wave][j];
@@ -577,8 +592,9 @@ __global__ __launch_bounds__(256) void k_edt_x(Grid g, const uint8_t *__restrict
 template <int AXIS>
 __global__ __launch_bounds__(256) void k_edt_axis(Grid g, const int32_t *__restrict__ in,
                                                   int32_t *__restrict__ out) {
-    const int x = (int)blockIdx.x * 64 + (threadIdx.x & 63),
-              y = (int)blockIdx.y * kRows + (threadIdx.x >> 6), z = (int)blockIdx.z;
+    const int sh = lane_log(g), rows = 64 >> sh, lane = threadIdx.x & 63;
+    const int x = (int)blockIdx.x * 64 + (lane & ((1 << sh) - 1)),
+              y = ((int)blockIdx.y * kRows + (threadIdx.x >> 6)) * rows + (lane >> sh), z = (int)blockIdx.z;
     if (x >= g.nx || y >= g.ny) return;
     const int64_t v = g.lin(x, y, z);
     const int64_t stride = AXIS == 1 ? (int64_t)g.nx : (int64_t)g.nx * g.ny;
@@ -964,11 +980,12 @@ extern "C" lbm_status lbm_pore_diameter(const int32_t n[3], const uint8_t *pore,
     int32_t *a = c.take<int32_t>(nv);
     int32_t *b = c.take<int32_t>(nv);
     CellInfo *info = c.take<CellInfo>((size_t)ncx * ncy * ncz);
-    k_edt_x<<<(unsigned)(((int64_t)g.ny * g.nz + kRows - 1) / kRows), 256, 0, s>>>(g, pore, a, emax_d);
+    const int64_t rows = kRows << (6 - lane_log(g));
+    k_edt_x<<<(unsigned)(((int64_t)g.ny * g.nz + rows - 1) / rows), 256, 0, s>>>(g, pore, a, emax_d);
     LBM_CHECK_LAUNCH();
-    k_edt_axis<1><<<row_grid(g), 256, 0, s>>>(g, a, b);
+    k_edt_axis<1><<<lane_grid(g), 256, 0, s>>>(g, a, b);
     LBM_CHECK_LAUNCH();
-    k_edt_axis<2><<<row_grid(g), 256, 0, s>>>(g, b, a);
+    k_edt_axis<2><<<lane_grid(g), 256, 0, s>>>(g, b, a);
     LBM_CHECK_LAUNCH();
     uint32_t *list = reinterpret_cast<uint32_t *>(b);
     k_mis_centres<<<dim3((unsigned)ncx, (unsigned)ncy, (unsigned)ncz), 512, 0, s>>>(g, a, emax_d, list,
