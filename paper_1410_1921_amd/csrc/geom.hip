@@ -25,14 +25,11 @@ constexpr int kRows = 4;
 
 // The distance passes give a wave several rows of a box of up to 32 voxels in x: rows of 2^lane_log
 // lanes each (nx = 1, ny = nz = 1000: 386 us for the three passes with a wave a row, now 20).
-__host__ __device__ inline int lane_log(const Grid &g) {
+// The number is the template argument LL, 6 for a row a wave, or -1 where it comes as `ll`.
+static int lane_log(const Grid &g) {
     int s = 0;
     while ((1 << s) < g.nx && s < 6) s++;
     return s;
-}
-static dim3 lane_grid(const Grid &g) {
-    const int rows = kRows << (6 - lane_log(g));
-    return dim3((unsigned)g.nseg, (unsigned)((g.ny + rows - 1) / rows), (unsigned)g.nz);
 }
 
 // ================================================================ labelling
@@ -542,10 +539,11 @@ __global__ __launch_bounds__(256) void k_chords(Grid g, const uint8_t *__restric
 // Squared distance to the nearest solid voxel along x: one wave per row, or several short
 // rows, from the bits of its segments.  (One thread per row, two scans of it, ran 7.7 ms at 512^3 on
 // uncoalesced rows; now 0.28 ms.)
-__global__ __launch_bounds__(256) void k_edt_x(Grid g, const uint8_t *__restrict__ pore,
+template <int LL>
+__global__ __launch_bounds__(256) void k_edt_x(Grid g, int ll, const uint8_t *__restrict__ pore,
                                                int32_t *__restrict__ out, int *__restrict__ emax) {
     __shared__ uint64_t solid[kRows][kMaxEdge / 64];
-    const int wave = threadIdx.x >> 6, sh = lane_log(g);
+    const int wave = threadIdx.x >> 6, sh = LL < 0 ? ll : LL;
     const int lane = threadIdx.x & ((1 << sh) - 1), first = (threadIdx.x & 63) - lane;  // of the row
     const int64_t row = ((int64_t)blockIdx.x * kRows + wave) * (64 >> sh) + (first >> sh);
     if (blockIdx.x == 0 && threadIdx.x == 0) *emax = 0;
@@ -557,12 +555,12 @@ __global__ __launch_bounds__(256) void k_edt_x(Grid g, const uint8_t *__restrict
         own = __ballot(live && x < g.nx && pore[base + x] == 0);
         if ((threadIdx.x & 63) == 0) solid[wave][k] = own;
     }
-    own = own >> first & (~0ull >> (64 - (1 << sh)));
+    if (LL < 0) own = own >> first & (~0ull >> (64 - (1 << sh)));
     __syncthreads();
     if (!live) return;
     int left = -kInf;  // last solid before this segment
     for (int k = 0; k < g.nseg; k++) {
-        const uint64_t w = g.nseg == 1 ? own : solid[wave][k];
+        const uint64_t w = LL < 0 ? own : solid[wave][k];  // short rows: of one segment
         int right = kInf;  // first solid after this segment
         for (int j = k + 1; j < g.nseg; j++) {
             const uint64_t n = solid[wave][j];
@@ -589,10 +587,10 @@ __global__ __launch_bounds__(256) void k_edt_x(Grid g, const uint8_t *__restrict
 // searched outwards from p until the distance term alone reaches the best value.  Bound by
 // the chain of those searches: 0.61-0.67 ms an axis at 512^3 (1.26 ms with one distance at
 // a time and the voxel's coordinates from 64-bit divisions).
-template <int AXIS>
-__global__ __launch_bounds__(256) void k_edt_axis(Grid g, const int32_t *__restrict__ in,
+template <int AXIS, int LL>
+__global__ __launch_bounds__(256) void k_edt_axis(Grid g, int ll, const int32_t *__restrict__ in,
                                                   int32_t *__restrict__ out) {
-    const int sh = lane_log(g), rows = 64 >> sh, lane = threadIdx.x & 63;
+    const int sh = LL < 0 ? ll : LL, rows = 64 >> sh, lane = threadIdx.x & 63;
     const int x = (int)blockIdx.x * 64 + (lane & ((1 << sh) - 1)),
               y = ((int)blockIdx.y * kRows + (threadIdx.x >> 6)) * rows + (lane >> sh), z = (int)blockIdx.z;
     if (x >= g.nx || y >= g.ny) return;
@@ -980,12 +978,23 @@ extern "C" lbm_status lbm_pore_diameter(const int32_t n[3], const uint8_t *pore,
     int32_t *a = c.take<int32_t>(nv);
     int32_t *b = c.take<int32_t>(nv);
     CellInfo *info = c.take<CellInfo>((size_t)ncx * ncy * ncz);
-    const int64_t rows = kRows << (6 - lane_log(g));
-    k_edt_x<<<(unsigned)(((int64_t)g.ny * g.nz + rows - 1) / rows), 256, 0, s>>>(g, pore, a, emax_d);
-    LBM_CHECK_LAUNCH();
-    k_edt_axis<1><<<lane_grid(g), 256, 0, s>>>(g, a, b);
-    LBM_CHECK_LAUNCH();
-    k_edt_axis<2><<<lane_grid(g), 256, 0, s>>>(g, b, a);
+    const int ll = lane_log(g);
+    const int64_t rows = kRows << (6 - ll);
+    const unsigned row_blocks = (unsigned)(((int64_t)g.ny * g.nz + rows - 1) / rows);
+    if (ll == 6) {
+        k_edt_x<6><<<row_blocks, 256, 0, s>>>(g, ll, pore, a, emax_d);
+        LBM_CHECK_LAUNCH();
+        k_edt_axis<1, 6><<<row_grid(g), 256, 0, s>>>(g, ll, a, b);
+        LBM_CHECK_LAUNCH();
+        k_edt_axis<2, 6><<<row_grid(g), 256, 0, s>>>(g, ll, b, a);
+    } else {
+        k_edt_x<-1><<<row_blocks, 256, 0, s>>>(g, ll, pore, a, emax_d);
+        LBM_CHECK_LAUNCH();
+        const dim3 grid(1, (unsigned)((g.ny + rows - 1) / rows), (unsigned)g.nz);
+        k_edt_axis<1, -1><<<grid, 256, 0, s>>>(g, ll, a, b);
+        LBM_CHECK_LAUNCH();
+        k_edt_axis<2, -1><<<grid, 256, 0, s>>>(g, ll, b, a);
+    }
     LBM_CHECK_LAUNCH();
     uint32_t *list = reinterpret_cast<uint32_t *>(b);
     k_mis_centres<<<dim3((unsigned)ncx, (unsigned)ncy, (unsigned)ncz), 512, 0, s>>>(g, a, emax_d, list,
