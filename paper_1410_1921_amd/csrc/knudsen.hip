@@ -326,9 +326,10 @@ __global__ __launch_bounds__(256) void k_sweep7(Sweep7 a) {
 // nodes without links, and it sends those of the others before it writes theirs.
 //
 // Per step, setup and the two plain sweeps of a check interval of 100 included: 128^3
-// (839 k nodes) 10.4 -> 4.8 us, of which 3.1 without the wait for packets (7.1 when every
-// wave sent its own packets, 5.6 before the work was put under their flight; 9.7 with
-// neighbouring workgroups on one XCD); 64^3 3.7 -> 2.5, 32^3 2.9 -> 2.2.
+// (840 k nodes) 10.1 -> 4.5 us, 64^3 4.0 -> 2.0, 32^3 3.8 -> 1.9.  (128^3 while the send lists
+// were still formed in every launch: 4.8, of which 3.1 without the wait for packets; 7.1 when
+// every wave sent its own packets, 5.6 before the work was put under their flight, 9.7 with
+// neighbouring workgroups on one XCD.)
 //
 // Every wait is bounded: a thread that waits longer than `limit` ticks (or sees another
 // one give up) sets *abort, its workgroup leaves at its next barrier, and so do the others

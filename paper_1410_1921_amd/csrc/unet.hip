@@ -510,8 +510,8 @@ __global__ __launch_bounds__(256) void k_transpose_w(const uint16_t *__restrict_
     wt[(t * cin + ci) * cout + co] = w[i];
 }
 
-// The elementwise layers take V consecutive channels per thread: V = 4 (one 8-byte
-// access) when the channel count, the strides and the pointers allow it, else V = 1.
+// The elementwise layers take V consecutive channels per thread: 8 (one 16-byte access) or 4
+// where the channel count, the strides and the pointers allow it, else 1.
 template <int V>
 __device__ inline void ldv(const uint16_t *p, uint16_t (&o)[V]) {
     if constexpr (V == 8) {
@@ -1061,9 +1061,10 @@ extern "C" lbm_status lbm_nn_conv3d_wgrad(const int32_t n[3], const uint16_t *x,
     const bool rows16 = x_cs % 8 == 0 && g_cs % 8 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(gy) % 16 == 0;
     if (g.nx % 4 == 0 && g.ny % 4 == 0 && g.nz % 4 == 0 && rows16) {
-        // two workgroups a compute unit, as far as the workspace's partial rows go: more only
-        // add rows to sum and a last round that is half empty (with the sum, 96^3 x 16 -> 16
-        // channels: 864 chunks 39.8 us, 494 32.8; 48^3 x 96 -> 32: 108 chunks 64.8, 40 36.0)
+        // two workgroups for each of the 256 compute units, as far as the workspace's partial
+        // rows go: more only add rows to sum and a last round that is half empty (with the sum,
+        // 96^3 x 16 -> 16 channels: 864 chunks 39.8 us, 494 32.8; 48^3 x 96 -> 32: 108 chunks
+        // 64.8, 40 36.0)
         const int64_t nb = (int64_t)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * (g.nz / 4);
         const int64_t blocks = (int64_t)(cout / 16) * (cin / 16);
         const int64_t rows = (int64_t)((ws_bytes - 256) / (((size_t)27 * cout * cin + cout) * sizeof(float)));
@@ -1076,18 +1077,18 @@ extern "C" lbm_status lbm_nn_conv3d_wgrad(const int32_t n[3], const uint16_t *x,
         LBM_CHECK_LAUNCH();
         nch = nbc;
     } else {
-    const dim3 grid((unsigned)nch, 27, (unsigned)(cout / 16));
-    switch (cin) {
-    case 16: k_conv3d_wgrad<1><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 32: k_conv3d_wgrad<2><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 48: k_conv3d_wgrad<3><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 64: k_conv3d_wgrad<4><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 96: k_conv3d_wgrad<6><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 128: k_conv3d_wgrad<8><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    case 192: k_conv3d_wgrad<12><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
-    default: set_error("lbm_nn_conv3d_wgrad: cin %d not supported", cin); return LBM_E_INVAL;
-    }
-    LBM_CHECK_LAUNCH();
+        const dim3 grid((unsigned)nch, 27, (unsigned)(cout / 16));
+        switch (cin) {
+        case 16: k_conv3d_wgrad<1><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 32: k_conv3d_wgrad<2><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 48: k_conv3d_wgrad<3><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 64: k_conv3d_wgrad<4><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 96: k_conv3d_wgrad<6><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 128: k_conv3d_wgrad<8><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        case 192: k_conv3d_wgrad<12><<<grid, 64, 0, s>>>(g, x, x_cs, gy, g_cs, cout, chunk, part, part_b); break;
+        default: set_error("lbm_nn_conv3d_wgrad: cin %d not supported", cin); return LBM_E_INVAL;
+        }
+        LBM_CHECK_LAUNCH();
     }
     sum_parts(part, nch, (int64_t)27 * cout * cin, dw, part_b, db ? cout : 0, db, accumulate, s);
     LBM_CHECK_LAUNCH();
