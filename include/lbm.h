@@ -25,9 +25,11 @@
  *  - Calls on different streams with different workspaces and outputs may run
  *    concurrently; the library keeps no global state besides the per-thread error
  *    string.  A Knudsen solve whose lattice fits the chip (D3Q7, variant 0, up to 1.06 M
- *    fluid nodes) runs each check interval as one cooperative launch that occupies every
- *    compute unit: other streams' work then runs between those launches (0.5 ms each at
- *    128^3 with check_every 100).  An explicit variant keeps to one short launch per step.
+ *    fluid nodes) runs each check interval as one launch that may occupy every compute unit:
+ *    other streams' work then runs beside what it leaves and between those launches (0.45 ms
+ *    each at 128^3 with check_every 100).  Where two such launches keep each other from
+ *    starting, both end after 0.5 ms and leave those steps, and the next intervals, to plain
+ *    sweeps.  An explicit variant keeps to one short launch per step.
  *  - Negative status values are errors (outputs unspecified); LBM_W_NOT_CONVERGED
  *    is a warning with every output filled at the step limit.  lbm_last_error()
  *    describes the most recent failure on the calling thread.

@@ -326,15 +326,20 @@ __global__ __launch_bounds__(256) void k_sweep7(Sweep7 a) {
 // nodes without links, and it sends those of the others before it writes theirs.
 //
 // Per step, setup and the two plain sweeps of a check interval of 100 included: 128^3
-// (840 k nodes) 10.1 -> 4.5 us, 64^3 4.0 -> 2.0, 32^3 3.8 -> 1.9.  (128^3 while the send lists
+// (840 k nodes) 10.1 -> 4.35 us, 64^3 3.9 -> 1.8, 32^3 3.6 -> 1.65.  (128^3 while the send lists
 // were still formed in every launch: 4.8, of which 3.1 without the wait for packets; 7.1 when
 // every wave sent its own packets, 5.6 before the work was put under their flight, 9.7 with
 // neighbouring workgroups on one XCD.)
 //
-// Every wait is bounded: a thread that waits longer than `limit` ticks (or sees another
-// one give up) sets *abort, its workgroup leaves at its next barrier, and so do the others
-// in their waits; the state read, src, is untouched and the caller runs plain sweeps from
-// it instead.  The launch is cooperative, so all workgroups are on the chip together.
+// Every wait is bounded: a thread that waits longer than `limit` ticks (or sees another one give
+// up) sets *abort, its workgroup leaves at its next barrier, and so do the others in their
+// waits; the state read, src, is untouched and the caller runs plain sweeps from it instead.
+// That is what ends a launch whose workgroups cannot all be on the chip together: another
+// solve's launch has some of its compute units, and each waits for workgroups that cannot
+// start.  Both then leave the next intervals to plain sweeps.  A cooperative launch would
+// promise them to be together, but it starts 20 us later and the queues of other streams
+// stood still beside it: eight streams of 64^3 flow and Knudsen solves took 196 ms, with plain
+// sweeps 74; eight Knudsen solves 183, with plain sweeps 35.  Launched as here 68 and 35.
 struct Res7 {
     Grid g;
     int64_t nf, stride;
@@ -349,6 +354,7 @@ struct Res7 {
     int *n_sends;
     int *abort;
     int64_t set;  // packet slots of a set
+    int silent;   // a workgroup that sends nothing (tests), or -1
     int threads, steps;
     uint32_t tag0;
     uint64_t limit;
@@ -464,7 +470,7 @@ __global__ __launch_bounds__(kResThreads + kResSenders) void k_resident7(Res7 a)
     __syncthreads();
     if (tid >= bd) {  // uniform per wave: the senders
         const uint2 *__restrict__ sends = a.sends + (int64_t)blockIdx.x * kResOut;
-        const int q = tid - bd, n = a.n_sends[blockIdx.x];
+        const int q = tid - bd, n = (int)blockIdx.x == a.silent ? 0 : a.n_sends[blockIdx.x];
         uint32_t from[kResSends], to[kResSends];
 #pragma unroll
         for (int e = 0; e < kResSends; e++) {
@@ -1173,24 +1179,27 @@ struct ResPlan {
     uint32_t tag = 1;    // step numbers used so far in the packets, plus one
     int cur = 0;         // buffer and steps of the last resident launch: what is run again
     int64_t steps = 0;   // with plain sweeps when it gave up
+    int plain_for = 0;    // intervals left to plain sweeps since a launch gave up,
+    int next_plain = 32;  // and after the next one
 };
 
 // Fewest steps of a resident launch, from the microseconds that a step takes either way.  A
-// launch costs 30 to 60 us more than a sweep (its cooperative start, rank lookups, filling and
-// emptying the LDS); a resident step is bound by the exchange, so by the 64-byte lines and the
-// packets of a workgroup, besides its nodes; a plain one by its launch, then by the cache.
-// Measured, plain and resident step, and the interval from which resident is the faster:
-//   20^3, porosity 0.5         3.6, 1.4 us     18 steps
-//   64^3, 0.45                 4.1, 1.8        18
-//   90 x 96 x 100, 0.40        5.6, 2.8        13
-//   128^3, 0.40               10.1, 4.3         8
-//   40 x 40 x 300, 0.5         5.3, 3.8        60 (rows along x: every neighbour row far away)
-//   24 x 24 x 1000, 0.5        5.2, 5.1        none up to 100
-//   16 x 64 x 700, 0.6         6.2, 6.6        none
+// launch costs 7 to 40 us more than its steps (rank lookups, filling and emptying the LDS); a
+// resident step is bound by the exchange, so by the 64-byte lines and the packets of a workgroup,
+// besides its nodes; a plain one by its launch, then by the cache.  Measured, plain and resident
+// step, and the check interval from which resident is the faster (its two plain sweeps included):
+//   20^3, porosity 0.5       2.8 to 3.6, 1.4 us    10 steps
+//   64^3, 0.45               3.5 to 4.2, 1.8       10
+//   64^3, all pore           4.4 to 4.8, 2.5       12
+//   128^3, 0.40             10.1, 4.3              10
+//   40 x 40 x 300, 0.5       4.6 to 5.3, 3.9       24 (rows along x: every neighbour row far away)
+//   24 x 24 x 1000, 0.5      5.2, 5.2              none up to 100
+//   16 x 64 x 700, 0.6       6.2, 6.5              none
 static int64_t resident_min_steps(int64_t nf, int groups, double lines, double packets) {
-    const double n = 1e-6 * (double)nf, plain = std::max(3.5 + 5.5 * n, 2.2 + 9.4 * n);
+    const double n = 1e-6 * (double)nf, plain = std::max(2.8 + 7.0 * n, 2.2 + 9.4 * n);
     const double res = 0.8 + (1.4e-3 * lines + 6e-4 * packets + 3.6e-4 * (double)nf) / groups;
-    return plain - res < 0.1 ? INT64_MAX : std::max<int64_t>(8, (int64_t)std::ceil(50.0 / (plain - res)));
+    const double gain = plain - res, launch = 10.0 + 35.0 * n;
+    return gain < 0.1 ? INT64_MAX : std::max<int64_t>(8, (int64_t)std::ceil(launch / gain));
 }
 
 // The resident sweeps are used where the whole lattice fits one workgroup per CU and the
@@ -1198,11 +1207,10 @@ static int64_t resident_min_steps(int64_t nf, int groups, double lines, double p
 // to a workgroup (below that the packets outweigh the nodes).
 static lbm_status resident_plan(int64_t nf, int32_t variant, int32_t lattice, ResPlan &r) {
     if (variant != 0 || lattice != LBM_LATTICE_D3Q7 || nf > kResNodes) return LBM_OK;
-    int dev = 0, cus = 0, coop = 0;
+    int dev = 0, cus = 0;
     LBM_TRY_HIP(hipGetDevice(&dev));
     LBM_TRY_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    LBM_TRY_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    if (!coop || cus < 1) return LBM_OK;
+    if (cus < 1) return LBM_OK;
     const int64_t groups = std::min<int64_t>(cus, kResGroups);
     const int64_t per = std::max<int64_t>((nf + groups - 1) / groups, 256);
     r.npt = (int)((per + kResThreads - 1) / kResThreads);
@@ -1230,6 +1238,7 @@ static Res7 resident_args(const KnWs &w, const Grid &g, int64_t nf, const Shift 
     a.n_sends = w.n_sends;
     a.abort = w.abort;
     a.set = (int64_t)r.groups * r.threads * kResLinks;
+    a.silent = -1;
     a.threads = r.threads;
     a.steps = 0;
     a.tag0 = r.tag;
@@ -1276,20 +1285,17 @@ static lbm_status resident_steps(const KnWs &w, const Grid &g, int64_t nf, const
     r.steps = steps;
     r.trace->launches++;
     r.trace->resident_steps += steps;
-    if (r.trace->give_up_at == r.trace->launches) {  // the first workgroup sends nothing
-        k_res_zero<<<1, 1, 0, s>>>(w.n_sends);
-        LBM_CHECK_LAUNCH();
-    }
+    if (r.trace->give_up_at == r.trace->launches) a.silent = 0;
     const void *kernel = r.npt == 1   ? reinterpret_cast<const void *>(&k_resident7<1>)
                          : r.npt == 2 ? reinterpret_cast<const void *>(&k_resident7<2>)
                          : r.npt == 3 ? reinterpret_cast<const void *>(&k_resident7<3>)
                          : r.npt == 4 ? reinterpret_cast<const void *>(&k_resident7<4>)
                                       : reinterpret_cast<const void *>(&k_resident7<5>);
     void *args[] = {&a};
-    // refused (fewer compute units than the device names, say): plain sweeps do the steps
+    // refused (more LDS than the device gives a workgroup, say): plain sweeps do the steps
     if (r.trace->refuse_at == r.trace->launches ||
-        hipLaunchCooperativeKernel(kernel, dim3((unsigned)r.groups),
-                                   dim3((unsigned)(r.threads + kResSenders)), args, 0, s) != hipSuccess) {
+        hipLaunchKernel(kernel, dim3((unsigned)r.groups), dim3((unsigned)(r.threads + kResSenders)), args, 0,
+                        s) != hipSuccess) {
         (void)hipGetLastError();
         r.on = false;
         r.trace->refused++;
@@ -1553,7 +1559,9 @@ static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const 
         LBM_TRY_HIP(hipEventRecord(e0, s));
         int *const gave_up = reinterpret_cast<int *>(pin.p + kKnSums);
         *gave_up = 0;
-        out = kn_launch(w, g, nf, h, mode, cur, pending, chunk, true, c_field, &res, s);
+        ResPlan *const resident = res.plain_for > 0 ? nullptr : &res;
+        if (!resident) res.plain_for--;
+        out = kn_launch(w, g, nf, h, mode, cur, pending, chunk, true, c_field, resident, s);
         for (;;) {
             if (out != LBM_OK) break;
             LBM_TRY_HIP(hipEventRecord(e1, s));
@@ -1570,12 +1578,15 @@ static lbm_status knudsen_solve(const int32_t n[3], const uint8_t *fluid, const 
             if (!res.on || !*gave_up) break;
             // the resident sweep gave up: its start, the frame and the snapshot are as they
             // were (the check did nothing), so plain sweeps run its steps and the check
-            res.on = false;
             res.trace->gave_up++;
             res.trace->resident_steps -= res.steps;
+            res.plain_for = res.next_plain;
+            res.next_plain = std::min(2 * res.next_plain, 4096);
+            k_res_zero<<<1, 1, 0, s>>>(w.abort);
+            LBM_CHECK_LAUNCH();
             cur = res.cur;
             pending = false;
-            out = kn_launch(w, g, nf, h, mode, cur, pending, res.steps + 1, true, c_field, &res, s);
+            out = kn_launch(w, g, nf, h, mode, cur, pending, res.steps + 1, true, c_field, nullptr, s);
         }
         if (out != LBM_OK) break;
         std::memcpy(sums, pin.p, sizeof(sums));

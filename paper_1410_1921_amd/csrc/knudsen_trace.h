@@ -8,9 +8,8 @@ namespace lbm {
 // What a Knudsen solve's resident sweeps did, and how the tests make one give up:
 // lbm_knudsen_solve_traced is lbm_knudsen_solve with this as one more argument.
 struct KnTrace {
-    // longest wait for a packet: 0.2 s of the 100 MHz clock (a step takes microseconds; work
-    // of other streams may hold a CU back for a while)
-    int64_t wait_ticks = 20000000;
+    // longest wait for a packet, in ticks of the 100 MHz clock
+    int64_t wait_ticks = 50000;
     int32_t give_up_at = 0;      // in this launch (1, 2, ..) one workgroup sends no packets,
     int32_t refuse_at = 0;       // this one counts as refused by the runtime
     int64_t resident_steps = 0;  // steps taken by resident sweeps

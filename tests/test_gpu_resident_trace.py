@@ -5,6 +5,7 @@ or the runtime refuses its launch, plain sweeps take its steps.  Fields against 
 step, bit for bit."""
 import ctypes as C
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -199,8 +200,9 @@ def test_no_lists_for_short_intervals(traced, every, first, then):
     assert (t.lists, t.launches) == then
 
 
-@pytest.mark.parametrize("shape,p,every,launches", [((20, 20, 20), 0.5, 12, 0), ((20, 20, 20), 0.5, 50, 2),
+@pytest.mark.parametrize("shape,p,every,launches", [((20, 20, 20), 0.5, 9, 0), ((20, 20, 20), 0.5, 50, 2),
                                                     ((128, 128, 128), 0.40, 14, 2),
+                                                    ((40, 40, 300), 0.5, 14, 0), ((40, 40, 300), 0.5, 100, 2),
                                                     ((16, 64, 700), 0.6, 100, 0), ((24, 24, 1000), 0.5, 100, 0)])
 def test_only_where_it_is_faster(traced, shape, p, every, launches):
     """The rule's clear cases: short intervals of a small lattice, and boxes whose workgroups have
@@ -212,3 +214,49 @@ def test_only_where_it_is_faster(traced, shape, p, every, launches):
     b, t = traced(g, d, min_steps=0, **kw)
     assert (t.launches, t.gave_up) == (launches, 0)
     assert torch.equal(a.field, b.field)
+
+
+def test_comes_back(traced):
+    """After a launch that gave up 32 intervals are left to plain sweeps, after the next one 64; the
+    packets and step numbers of the launches given up disturb no later one."""
+    m = W.blob_mask((40, 41, 42), 0.5, 5)
+    g, d, c0 = inputs(m, 6)
+    kw = dict(fixed_steps=300 * 30, check_every=30, want_c=True, c_init=c0, voxel_nm=2.0)
+    a = lbm.lbm_knudsen_solve(g, d, variant=PLAIN, **kw)
+    b, t = traced(g, d, wait=100_000, give_up_at=2, **kw)
+    # intervals 1 and 35 to 300 resident, 2 given up
+    assert (t.launches, t.gave_up, t.resident_steps) == (268, 1, 267 * 28)
+    same(a, b, m, 1)
+
+
+def test_many_streams_still_overlap():
+    """Eight solves on streams of their own against the same with plain sweeps, which overlap: about
+    as long (a launch that kept the other streams' queues off the device took five times that)."""
+    m = W.blob_mask((64, 64, 64), 0.40, 5)
+    jobs = [inputs(m, k) for k in range(8)]
+    kw = dict(fixed_steps=2000, check_every=100, voxel_nm=2.0, n_fluid=int(m.sum()))
+    size = lbm.lbm_workspace_size(lbm.LBM_WS_KNUDSEN, m.shape, kw["n_fluid"])
+    ws = [lbm.Workspace(size, jobs[0][0].device) for _ in jobs]
+    streams = [torch.cuda.Stream() for _ in jobs]
+    torch.cuda.synchronize()
+
+    def together(variant):
+        def work(k):
+            with torch.cuda.stream(streams[k]):
+                g, d, c0 = jobs[k]
+                lbm.lbm_knudsen_solve(g, d, c_init=c0, workspace=ws[k], variant=variant, **kw)
+        best = float("inf")
+        for _ in range(4):
+            threads = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+            t0 = time.perf_counter()
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+            best = min(best, time.perf_counter() - t0)
+        return best
+
+    plain = together(PLAIN | lbm.LBM_VARIANT_REMAP)
+    auto = together(lbm.LBM_VARIANT_AUTO)
+    print(f"plain {1e3 * plain:.1f} ms, auto {1e3 * auto:.1f} ms", flush=True)
+    assert auto < 2.5 * plain
