@@ -417,7 +417,7 @@ def batch_converge(lbm, W, count, net, max_edge=96):
             "stop_rule": {"tol": TOL, "flow_steady_dist": FLOW_STEADY,
                           "knudsen_flux_spread": KN_STEADY_EVAL},
             "form": "batched + warm-started Knudsen, binary32 state; binary16 is left out "
-                    "(on the 512^3 crop it is 1.19 x faster per sweep but 6e-3 off in k and "
+                    "(at 512^3 it is 1.30 x faster per sweep but 6e-3 off in k and "
                     "its residual stalls at its rounding floor, so it never meets the stop "
                     "rule)",
             "plain_s": round(t_plain, 2), "plain_flow_s": round(t_pf, 2),
